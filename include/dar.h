@@ -420,8 +420,8 @@ dar_status dar_attn_prefill_backward(const dar_shape* s, int T, const void* q, c
  *   dw_down); every output is overwritten, every reduction runs in a fixed
  *   order.
  *   ws: at least dar_prefill_rope_backward_workspace_bytes(s, T) bytes
- *   (caller-owned, overwritten): the rotated and lifted operands and fp32
- *   gradient arrays of the full-d distant keys.
+ *   (caller-owned, overwritten): the rotated and lifted operands, fp32 row
+ *   constants and the shares of the weight gradients.
  * Supported: bf16 with d in {64, 128}, any rotary_dim, d_down up to d (up to
  * 64 at d = 128); other shapes return DAR_E_UNSUPPORTED. */
 dar_status dar_attn_prefill_rope_backward(const dar_shape* s, int T, int pos0, const dar_rope* rope,

@@ -130,6 +130,34 @@ __device__ __forceinline__ void wg_share(const f32x16_t (&acc)[D / 32], float* p
     for (int idx = tid; idx < D * DD; idx += NW * 64) out[idx] = pbuf[idx];
 }
 
+// wg_share for one 32-column tile (columns c0 + 0..31, those below dd stored)
+// of a share of run-time width dd: pbuf holds [D][32]. The caller puts a
+// barrier after it before pbuf is used again.
+template <int D, int NW>
+__device__ __forceinline__ void wg_share_cols(const f32x16_t (&acc)[D / 32], float* pbuf, int wave,
+                                              int lane, int tid, int dd, int c0,
+                                              float* __restrict__ out) {
+    const int qc = lane & 31, hg = lane >> 5;
+#pragma unroll
+    for (int wv = 0; wv < NW; ++wv) {
+        if (wave == wv) {
+#pragma unroll
+            for (int t = 0; t < D / 32; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int e = 32 * t + 8 * (r >> 2) + 4 * hg + (r & 3);
+                    float* cell = pbuf + e * 32 + qc;
+                    *cell = (wv == 0) ? acc[t][r] : *cell + acc[t][r];
+                }
+        }
+        __syncthreads();
+    }
+    for (int idx = tid; idx < D * 32; idx += NW * 64) {
+        const int c = c0 + (idx & 31);
+        if (c < dd) out[(size_t)(idx >> 5) * dd + c] = pbuf[idx];
+    }
+}
+
 // Cooperative staging of a 64-row tile of two row-major [rows][D] bf16 arrays
 // through registers into LDS (rows at or past `n` read as zero): fetch() for
 // the next tile is issued before the current one is computed on, so its
@@ -1126,17 +1154,19 @@ hipError_t launch_bwd_mfma(const bf16_t* q, const bf16_t* k, const bf16_t* v, co
 // positions 0..Td-1, Td = T - w). The softmax is recomputed against the
 // forward's log-sum-exp:
 //   bwd_rope_rowprep_kernel  -lse (log2 units) and -delta = -dO . O per row
-//   bwd_rope_rows_kernel     dqr = s sum_j dS_ij key_ij over both regions
-//   bwd_rope_cols_kernel     per key, s sum_i dS_ij qr_i and sum_i P_ij dO_i over
-//                            the rows that see it in the window (dkr, dvw) or
-//                            at distance (dkd, dvd)
-//   bwd_rope_post_rows_kernel  dq = R^T dqr
-//   bwd_rope_post_keys_kernel  the rotation taken back (R^T) and the chain rule
-//                            through the lift x' = (x W_down) W_up for keys and
-//                            values, with the weight-gradient shares
+//   bwd_rope_rows_kernel     dqr = s sum_j dS_ij key_ij over both regions, then
+//                            dq = R^T dqr
+//   bwd_rope_keys_kernel     per key, s sum_i dS_ij qr_i and sum_i P_ij dO_i over
+//                            the rows that see it at distance (dkd, dvd) and in
+//                            the window (dkr, dvw); the rotation taken back and
+//                            the chain rule through the lift x' = (x W_down) W_up
+//                            for keys and values, with the weight-gradient shares
 //   bwd_wreduce_kernel       the shares summed in a fixed order
-// with s = 1/sqrt(d). The rows and cols kernels are the window kernels'
-// loops with the key range and mask of either region.
+// with s = 1/sqrt(d). The main loops are the window kernels' loops with the
+// key range and mask of either region; the key, row and latent gradients stay
+// in registers from the sums to the bf16 stores (written out in fp32 and read
+// back by separate rotation and chain-rule kernels they cost 135 MB and
+// 220 us at B4 H16 T2048 d64 d_down16 w128).
 
 namespace {
 
@@ -1171,21 +1201,109 @@ __global__ __launch_bounds__(256) void bwd_rope_rowprep_kernel(const bf16_t* __r
     nl2[(size_t)bh * Tr + i] = i < T ? -lse[(size_t)bh * T + i] * kLog2eB : 0.f;
 }
 
+// Dynamic LDS: the rows kernel's two tiles, or its wavefronts' fp32 rows; the
+// keys kernel's part below the weights (a wavefront's fp32 rows, or its bf16
+// tile with two latent tiles; the tiles and row constants fit in the same).
+__host__ __device__ constexpr int rope_rows_lds_bytes(int D, int NW) {
+    return 2 * 64 * (D + 8) * 2 > NW * 32 * (D + 4) * 4 ? 2 * 64 * (D + 8) * 2 : NW * 32 * (D + 4) * 4;
+}
+__host__ __device__ constexpr int rope_keys_scratch_bytes(int D, int NW) {
+    return NW * (32 * (D + 4) * 4 > 32 * (D + 8) * 2 + 2 * 32 * 40 * 2 ? 32 * (D + 4) * 4
+                                                                       : 32 * (D + 8) * 2 + 2 * 32 * 40 * 2);
+}
+static_assert(rope_keys_scratch_bytes(64, 4) >= 2 * 64 * 72 * 2 + 2 * 64 * 4 &&
+                  rope_keys_scratch_bytes(128, 4) >= 2 * 64 * 136 * 2 + 2 * 64 * 4 &&
+                  rope_keys_scratch_bytes(64, 4) >= 64 * 32 * 4 &&
+                  rope_keys_scratch_bytes(128, 4) >= 128 * 32 * 4,
+              "the row tiles and the share's sum fit in the scratch");
+
+// f x, then the rotation taken back (R_p^T: the pairs (m, m + r/2) turned by
+// -p base^(-2m/r); FWD: applied, R_p), for a wavefront's 32 tokens: accumulators in acc_row order
+// (register 8 h + u of tile tt holds element 32 tt + 16 h + 8 hg + u of token
+// qc). The pair's other element may sit in any register of either half, so
+// the rows go through the wavefront's LDS (F, 32 rows of D + 4 floats). tabp:
+// the angle row of this lane's token (r / 2 cos, then sin). Rotary dimensions
+// that are multiples of 16 turn whole runs of eight with vector loads.
+template <int D, bool FWD>
+__device__ __forceinline__ void rotate_tile(f32x16_t (&x)[D / 32], float f, float* F, int r,
+                                              const float* __restrict__ tabp, int qc, int hg) {
+    constexpr int NT = D / 32, LDF = D + 4;
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) x[tt][q] *= f;
+    if (r == 0) return;  // uniform
+    float* row = F + qc * LDF;
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+            for (int q = 0; q < 8; q += 4)
+                *reinterpret_cast<float4*>(row + 32 * tt + 16 * h2 + 8 * hg + q) =
+                    make_float4(x[tt][8 * h2 + q], x[tt][8 * h2 + q + 1], x[tt][8 * h2 + q + 2],
+                                x[tt][8 * h2 + q + 3]);
+    wave_lds_order();
+    const int h = r >> 1;
+    const bool runs = (r & 15) == 0;  // uniform
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) {
+            const int e0 = 32 * tt + 16 * h2 + 8 * hg;
+            if (32 * tt + 16 * h2 >= r) continue;  // uniform: both halves past the rotated part
+            if (runs) {
+                if (e0 < r) {
+                    const bool first = e0 < h;  // of its pair
+                    const int m = first ? e0 : e0 - h, o = first ? e0 + h : e0 - h;
+#pragma unroll
+                    for (int q = 0; q < 8; q += 4) {
+                        const float4 c = *reinterpret_cast<const float4*>(tabp + m + q);
+                        const float4 s = *reinterpret_cast<const float4*>(tabp + h + m + q);
+                        const float4 y = *reinterpret_cast<const float4*>(row + o + q);
+                        const float cc[4] = {c.x, c.y, c.z, c.w}, ss[4] = {s.x, s.y, s.z, s.w};
+                        const float yy[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+                        for (int z = 0; z < 4; ++z)
+                            x[tt][8 * h2 + q + z] =
+                                __builtin_fmaf(x[tt][8 * h2 + q + z], cc[z],
+                                               first != FWD ? yy[z] * ss[z] : -yy[z] * ss[z]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int z = 0; z < 8; ++z) {
+                    const int e = e0 + z;
+                    if (e < r) {
+                        const bool first = e < h;
+                        const int m = first ? e : e - h;
+                        const float y = row[first ? e + h : e - h], s = tabp[h + m];
+                        x[tt][8 * h2 + z] =
+                            __builtin_fmaf(x[tt][8 * h2 + z], tabp[m], first != FWD ? y * s : -y * s);
+                    }
+                }
+            }
+        }
+    wave_lds_order();
+}
+
 // One wavefront per 32 query rows: dqr^T += K^T dS^T over the window keys
 // (kr, v: i - w < j <= i) and the distant keys (kd, vd: j <= i - w), 64-key
-// tiles staged through LDS for the workgroup. Writes s dqr (fp32) of every
+// tiles staged through LDS for the workgroup. Writes dq = R^T (s dqr) of every
 // real row. Grid: ceil(T / (32 NW)) * B * Hq workgroups (xcd_block_head).
 template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) void bwd_rope_rows_kernel(
     const bf16_t* __restrict__ qr, const bf16_t* __restrict__ kr, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ kd, const bf16_t* __restrict__ vd, const bf16_t* __restrict__ dout,
-    const float* __restrict__ nl2, const float* __restrict__ nd, float* __restrict__ dqr, int Hq,
-    int Hkv, int T, int Tr, int w, float qscale, float scale, int BH) {
+    const float* __restrict__ nl2, const float* __restrict__ nd, const float* __restrict__ tab,
+    bf16_t* __restrict__ dq, int Hq, int Hkv, int T, int Tr, int w, int r, int pos0, float qscale,
+    float scale, int BH) {
     constexpr int KS = D / 16, NT = D / 32, BN = 64, LDK = D + 8;
     constexpr int BM = NW * 32;
-    __shared__ __attribute__((aligned(16))) bf16_t lds_kv[2 * BN * LDK];  // K tile, V tile
-    bf16_t* lds_k = lds_kv;
-    bf16_t* lds_v = lds_kv + BN * LDK;
+    // K tile and V tile, later each wavefront's fp32 rows for the rotation
+    extern __shared__ __align__(16) char sm[];
+    bf16_t* lds_k = reinterpret_cast<bf16_t*>(sm);
+    bf16_t* lds_v = lds_k + BN * LDK;
 
     const int tid = lane_id_x(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1259,8 +1377,8 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_rows_kernel(
                 const bf16x8_t s0 = pack8(ds, 0), s1 = pack8(ds, 8);
 #pragma unroll
                 for (int tt = 0; tt < NT; ++tt) {
-                    dqT[tt] = mfma(lds_tr_operand(lds_k, LDK, sub * 32, tt * 32, lane), s0, dqT[tt]);
-                    dqT[tt] = mfma(lds_tr_operand(lds_k, LDK, sub * 32 + 16, tt * 32, lane), s1, dqT[tt]);
+                    dqT[tt] = mfma(lds_tr_operand_perm(lds_k, LDK, sub * 32, tt * 32, lane), s0, dqT[tt]);
+                    dqT[tt] = mfma(lds_tr_operand_perm(lds_k, LDK, sub * 32 + 16, tt * 32, lane), s1, dqT[tt]);
                 }
             }
         }
@@ -1269,37 +1387,58 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_rows_kernel(
                       iwg_hi, false);
     if (iwg_hi - w >= 0) region(kd + (size_t)bg * Td * D, vd + (size_t)bg * Td * D, Td, 0, iwg_hi - w, true);
 
+    __syncthreads();  // the tiles are no longer read
+    rotate_tile<D, false>(dqT, scale, reinterpret_cast<float*>(sm) + wave * 32 * (D + 4), r,
+                     tab + (size_t)(pos0 + ii) * r, qc, hg);
     if (live && i < T) {
-        float* out = dqr + ((size_t)bh * T + i) * D;
+        bf16_t* out = dq + ((size_t)bh * T + i) * D + 8 * hg;
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
-                *reinterpret_cast<float4*>(out + tt * 32 + 8 * a + 4 * hg) =
-                    make_float4(dqT[tt][4 * a] * scale, dqT[tt][4 * a + 1] * scale,
-                                dqT[tt][4 * a + 2] * scale, dqT[tt][4 * a + 3] * scale);
+            for (int h2 = 0; h2 < 2; ++h2)
+                *reinterpret_cast<bf16x8_t*>(out + tt * 32 + h2 * 16) = pack8(dqT[tt], 8 * h2);
     }
 }
 
-// One wavefront per 32 keys of one region's key array (kx, vx: kr and v for
-// the window, kd and vd at distance, nkeys rows a head), the rows of every
-// query head of the group that see them there (window: j <= i < j + w; at
-// distance: i >= j + w) through 64-row Q / dO tiles in LDS:
-// dk^T += Q^T dS (times s), dv^T += dO^T P. Writes both (fp32) for every key.
-// Grid: ceil(nkeys / (32 NW)) * B * Hkv workgroups (xcd_block_head).
-template <int D, int NW, bool DIST>
-__global__ __launch_bounds__(NW * 64) void bwd_rope_cols_kernel(
-    const bf16_t* __restrict__ qr, const bf16_t* __restrict__ kx, const bf16_t* __restrict__ vx,
-    const bf16_t* __restrict__ dout, const float* __restrict__ nl2, const float* __restrict__ nd,
-    float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv, int T, int Tr, int nkeys,
-    int w, float qscale, float scale, int BKV) {
-    constexpr int KS = D / 16, NT = D / 32, BN = 64, LDK = D + 8;
+// One workgroup of NW wavefronts = 32 NW keys of one (batch, KV head), the
+// rows of every query head of the group that see them, through 64-row Q / dO
+// tiles in LDS: dk^T += Q^T dS, dv^T += dO^T P. First the rows at distance
+// (i >= j + w) against the lifted keys (kd, vd), then the window's rows
+// (j <= i < j + w) against (kr, v), each key's sums in one lane column. With
+// u = R^T s dkd between the two:
+//   gK = u W_up^T,  gV = dvd W_up^T,  cK = k W_down,  cV = v W_down
+//   dW_down += k^T gK + v^T gV,  dW_up^T += u^T cK + dvd^T cV  (shares)
+//   dk = R^T s dkr + gK W_down^T,  dv = dvw + gV W_down^T
+// on the matrix cores; u, dvd, gK, gV, cK, cV are fp32 sums and enter as bf16
+// hi + lo pairs (two fp32 factors as hi hi + hi lo + lo hi: about 16
+// significant bits, against the 8 of the P and dS they were summed from). The
+// chain rule adds about 75 products per wavefront to the 16 of each of its
+// 32-row subtiles (on the vector ALUs it took 190 us at B4 H16 T2048 d64
+// d_down16 w128; forward and backward together went from 550 to 346 us).
+// The window's sums start from gK W_down^T and gV W_down^T instead of keeping
+// gK and gV in registers through the window's loop. d_down <= 32 DT columns, zero padded. Writes the share of
+// chunk b * nkb + key block. Grid: ceil(T / (32 NW)) * B * Hkv workgroups
+// (xcd_block_head), key block 0 (most rows) first.
+template <int D, int DT, int NW>
+__global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
+    const bf16_t* __restrict__ qr, const bf16_t* __restrict__ kr, const bf16_t* __restrict__ v,
+    const bf16_t* __restrict__ kd, const bf16_t* __restrict__ vd, const bf16_t* __restrict__ dout,
+    const float* __restrict__ nl2, const float* __restrict__ nd, const bf16_t* __restrict__ k,
+    const bf16_t* __restrict__ wd, const bf16_t* __restrict__ wu, const float* __restrict__ tab,
+    bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, float* __restrict__ wpart, int Hq, int Hkv,
+    int T, int Tr, int dd, int w, int r, int pos0, float qscale, float scale, int nchunk, int BKV) {
+    constexpr int KS = D / 16, NT = D / 32, BN = 64, LDK = D + 8, LDH = 40;
     constexpr int BK = NW * 32;
-    __shared__ __attribute__((aligned(16))) bf16_t lds_qd[2 * BN * LDK];  // Q tile, dO tile
-    __shared__ __attribute__((aligned(16))) float lds_lse[BN];  // -lse (log2 units)
-    __shared__ __attribute__((aligned(16))) float lds_del[BN];  // -delta
-    bf16_t* lds_q = lds_qd;
-    bf16_t* lds_do = lds_qd + BN * LDK;
+    extern __shared__ __align__(16) char sm[];
+    // Q tile, dO tile, -lse and -delta of their rows; between and after the
+    // regions the wavefronts' scratch (fp32 rows for the rotation, or a bf16
+    // tile and two latent tiles) and the weight shares' sum
+    bf16_t* lds_q = reinterpret_cast<bf16_t*>(sm);
+    bf16_t* lds_do = lds_q + BN * LDK;
+    float* lds_lse = reinterpret_cast<float*>(lds_do + BN * LDK);
+    float* lds_del = lds_lse + BN;
+    bf16_t* wds = reinterpret_cast<bf16_t*>(sm + rope_keys_scratch_bytes(D, NW));  // W_down^T [c][e]
+    bf16_t* wus = wu ? wds + 32 * DT * LDK : wds;                                  // W_up [c][e]
 
     const int tid = lane_id_x(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1310,335 +1449,267 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_cols_kernel(
     const int qc = lane & 31, hg = lane >> 5, prow = perm_row(qc);
     const int cwg_lo = cb * BK;
     const int c0 = cwg_lo + wave * 32, j = c0 + qc;
-    const bool live = c0 < nkeys;
-    const int j_hi = imin(c0 + 31, nkeys - 1);
-    const int cwg_hi = imin(cwg_lo + BK - 1, nkeys - 1);
-    const int jj = imin(j, nkeys - 1);
+    const bool live = c0 < T;
+    const int jj = imin(j, T - 1);
+    const int Td = imax(T - w, 0);
 
-    bf16x8_t kop[KS], vop[KS];
-    const bf16_t* krow = kx + ((size_t)bg * nkeys + jj) * D;
-    const bf16_t* vrow = vx + ((size_t)bg * nkeys + jj) * D;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        kop[s] = load_bf16x8(krow + s * 16 + hg * 8);
-        vop[s] = load_bf16x8(vrow + s * 16 + hg * 8);
+    {
+        const bf16_t* wdg = wd + (size_t)g * D * dd;
+        const bf16_t* wug = wu ? wu + (size_t)g * dd * D : nullptr;
+        for (int idx = tid; idx < 32 * DT * D; idx += NW * 64) {
+            const int c = idx / D, e = idx % D, cc = imin(c, dd - 1);
+            const bf16_t x = wdg[(size_t)e * dd + cc];
+            wds[c * LDK + e] = c < dd ? x : (bf16_t)0;
+            if (wug) {
+                const bf16_t y = wug[(size_t)cc * D + e];
+                wus[c * LDK + e] = c < dd ? y : (bf16_t)0;
+            }
+        }
     }
+
     f32x16_t dkT[NT], dvT[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) { dkT[t] = splat16(0.f); dvT[t] = splat16(0.f); }
-    // the workgroup's rows: window [cwg_lo, cwg_hi + w - 1], at distance [cwg_lo + w, T - 1]
-    const int row_lo = DIST ? cwg_lo + w : cwg_lo;
-    const int row_hi = DIST ? T - 1 : imin(T - 1, cwg_hi + w - 1);
-    const int ntile = row_hi >= row_lo ? (row_hi - row_lo) / BN + 1 : 0;
-    TilePair<D, NW> tp;
-    float sv = 0.f;  // -lse (threads 0..63) or -delta (64..127) of one tile row
-    auto fetch = [&](int n) {
-        const int hh = n / ntile, t = row_lo + (n - hh * ntile) * BN;
-        const size_t bh = (size_t)b * Hq + g * G + hh;
-        tp.fetch(qr + bh * T * D, dout + bh * T * D, t, T, tid);
-        if (tid < 2 * BN) {
-            const int r = tid & (BN - 1);
-            const float* src = (tid < BN ? nl2 : nd) + bh * Tr;
-            sv = t + r < Tr ? src[imin(t + r, Tr - 1)] : 0.f;
+    // the sums over one region's rows, added to dkT, dvT (workgroup-uniform
+    // bounds: every thread reaches the barriers)
+    auto region = [&](const bf16_t* kx, const bf16_t* vx, int nkeys, bool dist) {
+        const int j_hi = imin(c0 + 31, nkeys - 1);
+        const int cwg_hi = imin(cwg_lo + BK - 1, nkeys - 1);
+        bf16x8_t kop[KS], vop[KS];
+        const bf16_t* krow = kx + ((size_t)bg * nkeys + imin(j, nkeys - 1)) * D;
+        const bf16_t* vrow = vx + ((size_t)bg * nkeys + imin(j, nkeys - 1)) * D;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            kop[s] = load_bf16x8(krow + s * 16 + hg * 8);
+            vop[s] = load_bf16x8(vrow + s * 16 + hg * 8);
         }
-    };
-    if (ntile > 0) fetch(0);
-    for (int n = 0; n < G * ntile; ++n) {
-        const int t = row_lo + (n % ntile) * BN;
-        __syncthreads();  // the previous tile is no longer read
-        tp.store(lds_q, lds_do, LDK, tid);
-        if (tid < BN) lds_lse[tid] = sv;
-        else if (tid < 2 * BN) lds_del[tid - BN] = sv;
-        __syncthreads();
-        if (n + 1 < G * ntile) fetch(n + 1);
-        if (!live) continue;
-#pragma unroll
-        for (int sub = 0; sub < BN / 32; ++sub) {
-            const int is = t + sub * 32;
-            if (DIST ? is + 31 < c0 + w : (is + 31 < c0 || is > j_hi + w - 1)) continue;
-            f32x16_t sc = splat16(0.f);
-            f32x16_t dp = load_row16(lds_del + sub * 32, hg, 1.f);
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                sc = mfma(load_bf16x8(lds_q + (sub * 32 + prow) * LDK + s * 16 + hg * 8), kop[s], sc);
-                dp = mfma(load_bf16x8(lds_do + (sub * 32 + prow) * LDK + s * 16 + hg * 8), vop[s], dp);
+        // the workgroup's rows: window [cwg_lo, cwg_hi + w - 1], at distance [cwg_lo + w, T - 1]
+        const int row_lo = dist ? cwg_lo + w : cwg_lo;
+        const int row_hi = dist ? T - 1 : imin(T - 1, cwg_hi + w - 1);
+        const int ntile = row_hi >= row_lo ? (row_hi - row_lo) / BN + 1 : 0;
+        TilePair<D, NW> tp;
+        float sv = 0.f;  // -lse (threads 0..63) or -delta (64..127) of one tile row
+        auto fetch = [&](int n) {
+            const int hh = n / ntile, t = row_lo + (n - hh * ntile) * BN;
+            const size_t bh = (size_t)b * Hq + g * G + hh;
+            tp.fetch(qr + bh * T * D, dout + bh * T * D, t, T, tid);
+            if (tid < 2 * BN) {
+                const int rr = tid & (BN - 1);
+                const float* src = (tid < BN ? nl2 : nd) + bh * Tr;
+                sv = t + rr < Tr ? src[imin(t + rr, Tr - 1)] : 0.f;
             }
-            const f32x16_t ln = load_row16(lds_lse + sub * 32, hg, 1.f);
-            f32x16_t x;
+        };
+        if (ntile > 0) fetch(0);
+        for (int n = 0; n < G * ntile; ++n) {
+            const int t = row_lo + (n % ntile) * BN;
+            __syncthreads();  // the previous tile is no longer read
+            tp.store(lds_q, lds_do, LDK, tid);
+            if (tid < BN) lds_lse[tid] = sv;
+            else if (tid < 2 * BN) lds_del[tid - BN] = sv;
+            __syncthreads();
+            if (n + 1 < G * ntile) fetch(n + 1);
+            if (!live) continue;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) x[r] = __builtin_fmaf(sc[r], qscale, ln[r]);
-            const bool full = DIST ? (is >= j_hi + w && is + 31 < T)
-                                   : (is >= c0 + 31 && is + 31 - c0 < w && is + 31 < T);
-            if (!full) {
+            for (int sub = 0; sub < BN / 32; ++sub) {
+                const int is = t + sub * 32;
+                if (dist ? is + 31 < c0 + w : (is + 31 < c0 || is > j_hi + w - 1)) continue;
+                f32x16_t sc = splat16(0.f);
+                f32x16_t dp = load_row16(lds_del + sub * 32, hg, 1.f);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int i = is + acc_row(r, hg);
-                    if (DIST ? (i - j < w || i >= T) : (i < j || i - j >= w || i >= T)) x[r] = -INFINITY;
+                for (int s = 0; s < KS; ++s) {
+                    sc = mfma(load_bf16x8(lds_q + (sub * 32 + prow) * LDK + s * 16 + hg * 8), kop[s], sc);
+                    dp = mfma(load_bf16x8(lds_do + (sub * 32 + prow) * LDK + s * 16 + hg * 8), vop[s], dp);
+                }
+                const f32x16_t ln = load_row16(lds_lse + sub * 32, hg, 1.f);
+                f32x16_t x;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) x[q] = __builtin_fmaf(sc[q], qscale, ln[q]);
+                const bool full = dist ? (is >= j_hi + w && is + 31 < T)
+                                       : (is >= c0 + 31 && is + 31 - c0 < w && is + 31 < T);
+                if (!full) {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) {
+                        const int i = is + acc_row(q, hg);
+                        if (dist ? (i - j < w || i >= T) : (i < j || i - j >= w || i >= T))
+                            x[q] = -INFINITY;
+                    }
+                }
+                f32x16_t p, ds;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    p[q] = __builtin_amdgcn_exp2f(x[q]);
+                    ds[q] = p[q] * dp[q];
+                }
+                const bf16x8_t p0 = pack8(p, 0), p1 = pack8(p, 8);
+                const bf16x8_t s0 = pack8(ds, 0), s1 = pack8(ds, 8);
+#pragma unroll
+                for (int tt = 0; tt < NT; ++tt) {
+                    dvT[tt] = mfma(lds_tr_operand_perm(lds_do, LDK, sub * 32, tt * 32, lane), p0, dvT[tt]);
+                    dvT[tt] = mfma(lds_tr_operand_perm(lds_do, LDK, sub * 32 + 16, tt * 32, lane), p1, dvT[tt]);
+                    dkT[tt] = mfma(lds_tr_operand_perm(lds_q, LDK, sub * 32, tt * 32, lane), s0, dkT[tt]);
+                    dkT[tt] = mfma(lds_tr_operand_perm(lds_q, LDK, sub * 32 + 16, tt * 32, lane), s1, dkT[tt]);
                 }
             }
-            f32x16_t p, ds;
+        }
+        __syncthreads();  // the tiles are no longer read (and the weights are staged)
+    };
+
+    float* F = reinterpret_cast<float*>(sm + wave * (rope_keys_scratch_bytes(D, NW) / NW));
+    bf16_t* xs = reinterpret_cast<bf16_t*>(F);  // [32][LDK]: 32 tokens at full d
+    bf16_t* yh = xs + 32 * LDK;                 // [32][LDH]: a 32-column latent tile, hi
+    bf16_t* yl = yh + 32 * LDH;                 // ... lo
+    const float* tabp = tab + (size_t)(pos0 + jj) * r;
+    const bool any_dist = live && c0 + w < T;  // wave-uniform
+    const int nkb = (T + BK - 1) / BK;
+    const size_t n_out = (size_t)D * dd;
+    const int chunk = b * nkb + cb;
+
+    if (Td > cwg_lo) region(kd, vd, Td, true);  // (workgroup-uniform) some key is distant for some row
+    else __syncthreads();                       // the weights are staged
+    rotate_tile<D, false>(dkT, scale, F, r, tabp, qc, hg);  // u
+    bf16x8_t uh[KS], ul[KS], dh[KS], dl[KS];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                p[r] = __builtin_amdgcn_exp2f(x[r]);
-                ds[r] = p[r] * dp[r];
-            }
-            const bf16x8_t p0 = pack8(p, 0), p1 = pack8(p, 8);
-            const bf16x8_t s0 = pack8(ds, 0), s1 = pack8(ds, 8);
+    for (int s = 0; s < KS; ++s) {
+        split8(dkT[s >> 1], 8 * (s & 1), 1.f, uh[s], ul[s]);
+        split8(dvT[s >> 1], 8 * (s & 1), 1.f, dh[s], dl[s]);
+    }
+    // gK W_down^T and gV W_down^T; the window's sums are added on top, the
+    // first (rotated forward, over s) in the rotated keys' frame
+#pragma unroll
+    for (int t = 0; t < NT; ++t) { dkT[t] = splat16(0.f); dvT[t] = splat16(0.f); }
+    const bf16_t* kp = k + ((size_t)bg * T + jj) * D + hg * 8;
+    const bf16_t* vp = v + ((size_t)bg * T + jj) * D + hg * 8;
+    // acc[e][c] += sum_j X[j][e] (Yh + Yl)[j][c], Y: columns c of token qc
+    auto put_y = [&](const bf16x8_t (&hi)[2], const bf16x8_t (&lo)[2]) {
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) {
+            *reinterpret_cast<bf16x8_t*>(yh + qc * LDH + 16 * h2 + 8 * hg) = hi[h2];
+            *reinterpret_cast<bf16x8_t*>(yl + qc * LDH + 16 * h2 + 8 * hg) = lo[h2];
+        }
+    };
+    auto share = [&](f32x16_t (&acc)[NT], const bf16x8_t (&x)[KS], bool with_lo) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            *reinterpret_cast<bf16x8_t*>(xs + qc * LDK + s * 16 + hg * 8) = x[s];
+        wave_lds_order();
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            const bf16x8_t bh = lds_tr_operand(yh, LDH, hf * 16, 0, lane);
+            const bf16x8_t bl = lds_tr_operand(yl, LDH, hf * 16, 0, lane);
 #pragma unroll
             for (int tt = 0; tt < NT; ++tt) {
-                dvT[tt] = mfma(lds_tr_operand(lds_do, LDK, sub * 32, tt * 32, lane), p0, dvT[tt]);
-                dvT[tt] = mfma(lds_tr_operand(lds_do, LDK, sub * 32 + 16, tt * 32, lane), p1, dvT[tt]);
-                dkT[tt] = mfma(lds_tr_operand(lds_q, LDK, sub * 32, tt * 32, lane), s0, dkT[tt]);
-                dkT[tt] = mfma(lds_tr_operand(lds_q, LDK, sub * 32 + 16, tt * 32, lane), s1, dkT[tt]);
+                const bf16x8_t a = lds_tr_operand(xs, LDK, hf * 16, tt * 32, lane);
+                if (with_lo) acc[tt] = mfma(a, bl, acc[tt]);
+                acc[tt] = mfma(a, bh, acc[tt]);
             }
         }
+        wave_lds_order();
+    };
+#pragma unroll
+    for (int ct = 0; ct < DT; ++ct)
+#pragma unroll
+        for (int up = 0; up < 2; ++up) {
+            f32x16_t pw[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) pw[t] = splat16(0.f);
+            if (any_dist) {
+                // up 0: gK, gV; 1: cK, cV (32 columns of this lane's token)
+                f32x16_t yk = splat16(0.f), yv = splat16(0.f);
+                bf16x8_t kB[KS], vB[KS], kh[2], kl[2], vh[2], vl[2];
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    kB[s] = load_bf16x8(kp + s * 16);
+                    vB[s] = load_bf16x8(vp + s * 16);
+                }
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const bf16x8_t a =
+                        load_bf16x8((up ? wds : wus) + (32 * ct + prow) * LDK + s * 16 + hg * 8);
+                    if (up == 0) {
+                        yk = mfma(a, ul[s], yk);
+                        yv = mfma(a, dl[s], yv);
+                    }
+                    yk = mfma(a, up ? kB[s] : uh[s], yk);
+                    yv = mfma(a, up ? vB[s] : dh[s], yv);
+                }
+#pragma unroll
+                for (int h2 = 0; h2 < 2; ++h2) {
+                    split8(yk, 8 * h2, 1.f, kh[h2], kl[h2]);
+                    split8(yv, 8 * h2, 1.f, vh[h2], vl[h2]);
+                }
+                wave_lds_order();
+                put_y(kh, kl);
+                if (up) share(pw, ul, false);
+                share(pw, up ? uh : kB, true);
+                put_y(vh, vl);
+                if (up) share(pw, dl, false);
+                share(pw, up ? dh : vB, true);
+                if (up == 0) {
+#pragma unroll
+                    for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+                        for (int tt = 0; tt < NT; ++tt) {
+                            const bf16x8_t a =
+                                lds_tr_operand_perm(wds, LDK, 32 * ct + 16 * h2, 32 * tt, lane);
+                            dkT[tt] = mfma(a, kl[h2], dkT[tt]);
+                            dvT[tt] = mfma(a, vl[h2], dvT[tt]);
+                            dkT[tt] = mfma(a, kh[h2], dkT[tt]);
+                            dvT[tt] = mfma(a, vh[h2], dvT[tt]);
+                        }
+                }
+            }
+            // the wavefronts' shares added in order (pbuf is the scratch)
+            __syncthreads();
+            wg_share_cols<D, NW>(pw, reinterpret_cast<float*>(sm), wave, lane, tid, dd, 32 * ct,
+                                 wpart + ((size_t)(up ? Hkv + g : g) * nchunk + chunk) * n_out);
+            __syncthreads();
+        }
+
+    if (w > 0) {
+        rotate_tile<D, true>(dkT, 1.f / scale, F, r, tabp, qc, hg);
+        __syncthreads();  // the scratch becomes the tiles
+        region(kr, v, T, false);
+        rotate_tile<D, false>(dkT, scale, F, r, tabp, qc, hg);
     }
-    if (live && j < nkeys) {
-        float* dkr = dk + ((size_t)bg * nkeys + j) * D;
-        float* dvr = dv + ((size_t)bg * nkeys + j) * D;
+    if (live && j < T) {
+        bf16_t* dkr = dk + ((size_t)bg * T + j) * D + 8 * hg;
+        bf16_t* dvr = dv + ((size_t)bg * T + j) * D + 8 * hg;
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                *reinterpret_cast<float4*>(dkr + tt * 32 + 8 * a + 4 * hg) =
-                    make_float4(dkT[tt][4 * a] * scale, dkT[tt][4 * a + 1] * scale,
-                                dkT[tt][4 * a + 2] * scale, dkT[tt][4 * a + 3] * scale);
-                *reinterpret_cast<float4*>(dvr + tt * 32 + 8 * a + 4 * hg) =
-                    make_float4(dvT[tt][4 * a], dvT[tt][4 * a + 1], dvT[tt][4 * a + 2], dvT[tt][4 * a + 3]);
+            for (int h2 = 0; h2 < 2; ++h2) {
+                *reinterpret_cast<bf16x8_t*>(dkr + tt * 32 + h2 * 16) = pack8(dkT[tt], 8 * h2);
+                *reinterpret_cast<bf16x8_t*>(dvr + tt * 32 + h2 * 16) = pack8(dvT[tt], 8 * h2);
             }
     }
 }
 
-// Element e of R_p^T x for a row x at position p: the rotation taken back,
-// pairs (m, m + r/2) turned by -p base^(-2m/r) (tab [n_pos][r]: cos, then sin).
-__device__ __forceinline__ float rot_back(const float* x, int e, int r, const float* tabp) {
-    const int h = r >> 1;
-    if (e >= r) return x[e];
-    const int m = e < h ? e : e - h;
-    const float c = tabp[m], s = tabp[h + m];
-    return e < h ? __builtin_fmaf(x[e], c, x[e + h] * s) : __builtin_fmaf(x[e], c, -x[e - h] * s);
-}
-
-// dq = R^T dqr (bf16). One thread per element; grid (ceil(T D / 256), B Hq),
-// so that the row and element come from shifts by the compile-time D rather
-// than 64-bit divisions.
-template <int D>
-__global__ __launch_bounds__(256) void bwd_rope_post_rows_kernel(const float* __restrict__ dqr,
-                                                                 const float* __restrict__ tab,
-                                                                 bf16_t* __restrict__ dq, int T,
-                                                                 int r, int pos0) {
-    const int idx = wg_id_x() * 256 + lane_id_x();
-    if (idx >= T * D) return;
-    const int i = idx / D, e = idx % D;
-    const size_t row = (size_t)wg_id_y() * T + i;
-    dq[row * D + e] = f32_to_bf16(rot_back(dqr + row * D, e, r, tab + (size_t)(pos0 + i) * r));
-}
-
-// The chain rule per key, and the weight-gradient shares. A workgroup takes
-// kRopeKeysPerWg keys of one (batch, KV head) in blocks of rope_post_block(D); per key j
-// (u_j = R^T dkd_j and dvd_j zero at or past Td = T - w):
-//   gK_j = u_j W_up^T,  gV_j = dvd_j W_up^T,  cK_j = k_j W_down,  cV_j = v_j W_down
-//   dk_j = R^T dkr_j + gK_j W_down^T,  dv_j = dvw_j + gV_j W_down^T   (bf16)
-// and over its keys, in key order, the shares [e][c]
-//   dW_down += k_j[e] gK_j[c] + v_j[e] gV_j[c]
-//   dW_up^T += u_j[e] cK_j[c] + dvd_j[e] cV_j[c]
-// (chunk b * ceil(T / kRopeKeysPerWg) + workgroup). d_down <= D.
-constexpr int kRopeKeysPerWg = 32;
-
-// Keys per block of bwd_rope_post_keys_kernel (32 measured slower at d = 64:
-// 310 against 256 us at the pythia70m shape), and its dynamic LDS in floats:
-// a [KB][D + 1] block of four-float key entries (rows padded by one entry:
-// the lanes reading one column of different rows hit different banks), four
-// [KB][dd] latent blocks, the two weights interleaved and W_down transposed.
-__host__ __device__ constexpr int rope_post_block(int) { return 16; }
-static inline size_t rope_post_lds_bytes(int D, int dd) {
-    const size_t kb = rope_post_block(D);
-    return sizeof(float) * (4 * kb * (D + 1) + 4 * kb * dd + (size_t)3 * D * dd);
-}
-
-// NO bounds the weight columns a thread owns (cpt = ceil(d_down / (256 / D))),
-// chosen at launch from d_down so that the share loop unrolls over registers
-// that exist: sized for the largest d_down it would hold 16 (d = 64) or 64
-// (d = 128) accumulator pairs and halve the occupancy.
-template <int D, int NO>
-__global__ __launch_bounds__(256) void bwd_rope_post_keys_kernel(
-    const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, const bf16_t* __restrict__ wd,
-    const bf16_t* __restrict__ wu, const float* __restrict__ dkr, const float* __restrict__ dvw,
-    const float* __restrict__ dkd, const float* __restrict__ dvd, const float* __restrict__ tab,
-    bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, float* __restrict__ wpart, int Hkv, int T,
-    int dd, int w, int r, int pos0, int nchunk) {
-    constexpr int KB = rope_post_block(D);
-    constexpr int XJ = KB * D / 256, JS = 256 / D;  // keys of a thread in dk/dv, their stride
-    extern __shared__ __align__(16) float sm[];
-    constexpr int LD = D + 1;         // padded key row
-    // the four key-side values of one (key, element) side by side, and the
-    // two weights of one (e, c): one 16-byte and one 8-byte LDS read feed the
-    // four products of an element
-    float4* sx = reinterpret_cast<float4*>(sm);  // [KB][LD]  (u = R^T dkd, dvd, k, v)
-    float* sg = sm + 4 * KB * LD;                // [4][KB][dd]  gK, gV, cK, cV
-    float2* sw = reinterpret_cast<float2*>(sg + 4 * KB * dd);  // [D][dd]  (W_up[c][e], W_down[e][c])
-    float* swt = sg + 4 * KB * dd + 2 * D * dd;  // [dd][D]  W_down[e][c] at [c][e]
-    const int bg = wg_id_y(), b = bg / Hkv, g = bg % Hkv;
-    const int tid = lane_id_x();
-    const int Td = imax(T - w, 0);
-    const int nkb = (T + kRopeKeysPerWg - 1) / kRopeKeysPerWg;
-    const int j_lo = wg_id_x() * kRopeKeysPerWg;
-    const int j_end = imin(j_lo + kRopeKeysPerWg, T);
-    const bf16_t* wdg = wd + (size_t)g * D * dd;
-    const bf16_t* wug = wu ? wu + (size_t)g * dd * D : nullptr;
-    const int n_out = D * dd;
-    // weight shares: TPE threads per element e, cpt columns each
-    constexpr int TPE = 256 / D;
-    const int we = tid / TPE, wq = tid % TPE;
-    const int cpt = (dd + TPE - 1) / TPE;  // <= NO (checked at launch)
-    for (int idx = tid; idx < n_out; idx += 256) {
-        const int e = idx / dd, c = idx - (idx / dd) * dd;
-        const float x = bf16_to_f32(wdg[idx]);
-        swt[c * D + e] = x;
-        sw[idx] = make_float2(wug ? bf16_to_f32(wug[(size_t)c * D + e]) : x, x);
-    }
-    float accd[NO], accu[NO];
-#pragma unroll
-    for (int x = 0; x < NO; ++x) accd[x] = accu[x] = 0.f;
-    for (int j0 = j_lo; j0 < j_end; j0 += KB) {
-        __syncthreads();  // the weights are staged; the previous block is no longer read
-        // stage: u = R^T dkd, dvd, k, v of the block's keys (zero past the ends)
-        for (int idx = tid; idx < KB * D; idx += 256) {
-            const int jl = idx / D, e = idx - (idx / D) * D, j = j0 + jl;
-            float uu = 0.f, vd = 0.f, kk = 0.f, vv = 0.f;
-            if (j < j_end) {
-                const size_t row = (size_t)bg * T + j;
-                kk = bf16_to_f32(k[row * D + e]);
-                vv = bf16_to_f32(v[row * D + e]);
-                if (j < Td) {
-                    const size_t drow = (size_t)bg * Td + j;
-                    uu = rot_back(dkd + drow * D, e, r, tab + (size_t)(pos0 + j) * r);
-                    vd = dvd[drow * D + e];
-                }
-            }
-            sx[jl * LD + e] = make_float4(uu, vd, kk, vv);
-        }
-        __syncthreads();
-        // gK, gV (through W_up) and cK, cV (through W_down), d_down wide: the
-        // four products of one (key, column) together (independent chains)
-        for (int idx = tid; idx < KB * dd; idx += 256) {
-            const int jl = idx / dd, c = idx - (idx / dd) * dd;
-            float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-#pragma unroll 8
-            for (int e = 0; e < D; ++e) {
-                const float2 wt = sw[e * dd + c];  // (W_up, W_down)
-                const float4 xv = sx[jl * LD + e];
-                a0 = __builtin_fmaf(xv.x, wt.x, a0);
-                a1 = __builtin_fmaf(xv.y, wt.x, a1);
-                a2 = __builtin_fmaf(xv.z, wt.y, a2);
-                a3 = __builtin_fmaf(xv.w, wt.y, a3);
-            }
-            sg[idx] = a0;
-            sg[KB * dd + idx] = a1;
-            sg[2 * KB * dd + idx] = a2;
-            sg[3 * KB * dd + idx] = a3;
-        }
-        __syncthreads();
-        // dk, dv of the block's keys: a thread keeps one element e of XJ keys,
-        // so each weight it reads serves all of them
-        {
-            const int e = tid % D, jl0 = tid / D;
-            float xk[XJ], xv[XJ];
-#pragma unroll
-            for (int x = 0; x < XJ; ++x) {
-                const int j = imin(j0 + jl0 + JS * x, j_end - 1);
-                const size_t row = (size_t)bg * T + j;
-                xk[x] = rot_back(dkr + row * D, e, r, tab + (size_t)(pos0 + j) * r);
-                xv[x] = dvw[row * D + e];
-            }
-            for (int c = 0; c < dd; ++c) {
-                const float wdn = swt[c * D + e];
-#pragma unroll
-                for (int x = 0; x < XJ; ++x) {
-                    xk[x] = __builtin_fmaf(sg[(jl0 + JS * x) * dd + c], wdn, xk[x]);
-                    xv[x] = __builtin_fmaf(sg[(KB + jl0 + JS * x) * dd + c], wdn, xv[x]);
-                }
-            }
-#pragma unroll
-            for (int x = 0; x < XJ; ++x) {
-                const int j = j0 + jl0 + JS * x;
-                if (j < j_end) {
-                    const size_t row = (size_t)bg * T + j;
-                    dk[row * D + e] = f32_to_bf16(xk[x]);
-                    dv[row * D + e] = f32_to_bf16(xv[x]);
-                }
-            }
-        }
-        // weight shares, key by key in order: a thread owns element e and the
-        // columns [q cpt, q cpt + cpt) (independent chains; columns past
-        // d_down are clamped and never stored)
-#pragma unroll 1  // unrolled, its hoisted reads take the registers of a wave per SIMD
-        for (int jl = 0; jl < KB; ++jl) {
-            const float4 xv = sx[jl * LD + we];
-            const float u_ = xv.x, d_ = xv.y, k_ = xv.z, v_ = xv.w;
-            const float* g0 = sg + jl * dd;
-            // a guard rather than a break: with a fixed trip count the loop
-            // unrolls and accd / accu stay in statically named registers
-#pragma unroll
-            for (int y = 0; y < NO; ++y) {
-                if (y < cpt) {  // uniform
-                    const int c = imin(wq * cpt + y, dd - 1);
-                    accd[y] = __builtin_fmaf(k_, g0[c], accd[y]);
-                    accd[y] = __builtin_fmaf(v_, g0[KB * dd + c], accd[y]);
-                    accu[y] = __builtin_fmaf(u_, g0[2 * KB * dd + c], accu[y]);
-                    accu[y] = __builtin_fmaf(d_, g0[3 * KB * dd + c], accu[y]);
-                }
-            }
-        }
-    }
-    const int chunk = b * nkb + wg_id_x();
-    float* pd = wpart + ((size_t)g * nchunk + chunk) * n_out;
-    float* pu = wpart + ((size_t)(Hkv + g) * nchunk + chunk) * n_out;
-#pragma unroll
-    for (int y = 0; y < NO; ++y) {
-        const int c = wq * cpt + y;
-        if (y < cpt && c < dd) {
-            pd[we * dd + c] = accd[y];
-            pu[we * dd + c] = accu[y];
-        }
-    }
+// Above 64 KB a kernel's dynamic LDS has to be asked for.
+hipError_t allow_lds(const void* fn, int bytes) {
+    if (bytes <= 65536) return hipSuccess;
+    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 }  // namespace
 
-// (the post kernel's LDS, within the 160 KB of a compute unit: d_down <= 64 at d = 128)
+// d_down up to d, and at d = 128 up to 73
 bool bwd_rope_mfma_supported(int d, int dd, bool bf16) {
-    return bf16 && (d == 64 || d == 128) && dd <= d && rope_post_lds_bytes(d, dd) <= 160 * 1024;
+    return bf16 && ((d == 64 && dd <= 64) || (d == 128 && dd <= 73));
 }
 
-template <int D, int NO>
-static hipError_t launch_rope_post_keys_t(const RopeBwdArgs& a, hipStream_t st) {
-    const int nkb = (a.T + kRopeKeysPerWg - 1) / kRopeKeysPerWg;
-    const size_t plds = rope_post_lds_bytes(D, a.dd);
-    if (plds > 65536) {
-        const hipError_t e = hipFuncSetAttribute((const void*)bwd_rope_post_keys_kernel<D, NO>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)plds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((bwd_rope_post_keys_kernel<D, NO>), dim3(nkb, a.B * a.Hkv), dim3(256), plds, st,
-                       a.k, a.v, a.wd, a.wu, (const float*)a.dkr, (const float*)a.dvw,
-                       (const float*)a.dkd, (const float*)a.dvd, a.tab, a.dk, a.dv, a.wpart, a.Hkv,
-                       a.T, a.dd, a.w, a.r, a.pos0, a.L.nchunk);
+template <int D, int DT, int NW>
+static hipError_t launch_rope_keys_t(const RopeBwdArgs& a, hipStream_t st) {
+    const int nkb = (a.T + NW * 32 - 1) / (NW * 32);
+    const float scale = 1.f / sqrtf((float)D);
+    const int lds = rope_keys_scratch_bytes(D, NW) + (a.wu ? 2 : 1) * 32 * DT * (D + 8) * 2;
+    const hipError_t e = allow_lds((const void*)bwd_rope_keys_kernel<D, DT, NW>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((bwd_rope_keys_kernel<D, DT, NW>), dim3(nkb * a.B * a.Hkv), dim3(NW * 64), lds,
+                       st, a.qr, a.kr, a.v, a.kd, a.vd, a.dout, (const float*)a.nl2,
+                       (const float*)a.nd, a.k, a.wd, a.wu, a.tab, a.dk, a.dv, a.wpart, a.Hq, a.Hkv,
+                       a.T, round_up(a.T, 64), a.dd, a.w, a.r, a.pos0, scale * kLog2eB, scale,
+                       a.L.nchunk, a.B * a.Hkv);
     return hipGetLastError();
-}
-
-// the smallest column bound that holds ceil(d_down / (256 / D)); d_down <= D
-template <int D>
-static hipError_t launch_rope_post_keys(const RopeBwdArgs& a, hipStream_t st) {
-    const int cpt = (a.dd + 256 / D - 1) / (256 / D);
-    if (cpt <= 4) return launch_rope_post_keys_t<D, 4>(a, st);
-    if (cpt <= 8) return launch_rope_post_keys_t<D, 8>(a, st);
-    if (cpt <= 16) return launch_rope_post_keys_t<D, 16>(a, st);
-    if constexpr (D * D / 256 > 16) {
-        if (cpt <= 32) return launch_rope_post_keys_t<D, 32>(a, st);
-        if (cpt <= D * D / 256) return launch_rope_post_keys_t<D, D * D / 256>(a, st);
-    }
-    return hipErrorInvalidValue;
 }
 
 template <int D>
@@ -1646,28 +1717,21 @@ static hipError_t launch_bwd_rope_t(const RopeBwdArgs& a, hipStream_t st) {
     constexpr int NW = 4;
     const int B = a.B, Hq = a.Hq, Hkv = a.Hkv, T = a.T, w = a.w, dd = a.dd, r = a.r;
     const int Tr = round_up(T, 64);
-    const int Td = T - w > 0 ? T - w : 0;
     const float scale = 1.f / sqrtf((float)D);
     const float qscale = scale * kLog2eB;
-    const int BM = NW * 32;
-    const int nblk = (T + BM - 1) / BM;
+    const int nblk = (T + NW * 32 - 1) / (NW * 32);
     hipLaunchKernelGGL(bwd_rope_rowprep_kernel<D>, dim3((Tr + 255) / 256, B * Hq), dim3(256), 0, st, a.o, a.dout,
                        a.lse, a.nl2, a.nd, T, Tr);
-    hipLaunchKernelGGL((bwd_rope_rows_kernel<D, NW>), dim3(nblk * B * Hq), dim3(NW * 64), 0, st, a.qr,
-                       a.kr, a.v, a.kd, a.vd, a.dout, (const float*)a.nl2, (const float*)a.nd, a.dqr, Hq,
-                       Hkv, T, Tr, w, qscale, scale, B * Hq);
-    hipLaunchKernelGGL((bwd_rope_cols_kernel<D, NW, false>), dim3(nblk * B * Hkv), dim3(NW * 64), 0, st,
-                       a.qr, a.kr, a.v, a.dout, (const float*)a.nl2, (const float*)a.nd, a.dkr, a.dvw,
-                       Hq, Hkv, T, Tr, T, w, qscale, scale, B * Hkv);
-    if (Td > 0) {
-        const int nkb = (Td + BM - 1) / BM;
-        hipLaunchKernelGGL((bwd_rope_cols_kernel<D, NW, true>), dim3(nkb * B * Hkv), dim3(NW * 64), 0, st,
-                           a.qr, a.kd, a.vd, a.dout, (const float*)a.nl2, (const float*)a.nd, a.dkd,
-                           a.dvd, Hq, Hkv, T, Tr, Td, w, qscale, scale, B * Hkv);
-    }
-    hipLaunchKernelGGL(bwd_rope_post_rows_kernel<D>, dim3((T * D + 255) / 256, B * Hq), dim3(256), 0,
-                       st, (const float*)a.dqr, a.tab, a.dq, T, r, a.pos0);
-    const hipError_t e = launch_rope_post_keys<D>(a, st);
+    const int rlds = rope_rows_lds_bytes(D, NW);
+    hipError_t e = allow_lds((const void*)bwd_rope_rows_kernel<D, NW>, rlds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((bwd_rope_rows_kernel<D, NW>), dim3(nblk * B * Hq), dim3(NW * 64), rlds, st,
+                       a.qr, a.kr, a.v, a.kd, a.vd, a.dout, (const float*)a.nl2, (const float*)a.nd,
+                       a.tab, a.dq, Hq, Hkv, T, Tr, w, r, a.pos0, qscale, scale, B * Hq);
+    if (dd <= 32) e = launch_rope_keys_t<D, 1, NW>(a, st);
+    else if (dd <= 64) e = launch_rope_keys_t<D, 2, NW>(a, st);
+    else if constexpr (D == 128) e = launch_rope_keys_t<D, 3, NW>(a, st);
+    else e = hipErrorInvalidValue;
     if (e != hipSuccess) return e;
     return launch_bwd_wreduce(a.wpart, a.dwd, a.dwu, Hkv, D, dd, a.L, st);
 }

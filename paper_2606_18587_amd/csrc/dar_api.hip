@@ -243,9 +243,10 @@ struct ChunkPagedWs {
 
 // Backward with the rotary embedding: the rotary pre-pass's arrays (bf16:
 // rotated queries and keys, lifted and rotated distant keys, lifted values),
-// then the fp32 arrays of RopeBwdArgs; every part 256-byte aligned.
+// then the fp32 row constants and weight-gradient shares of RopeBwdArgs; every
+// part 256-byte aligned.
 struct RopeBwdWs {
-    size_t qr, kr, kd, vd, nl2, nd, dqr, dkr, dvw, dkd, dvd, wpart, bytes;
+    size_t qr, kr, kd, vd, nl2, nd, wpart, bytes;
     int nchunk;
 };
 
@@ -263,12 +264,7 @@ RopeBwdWs rope_bwd_ws_layout(const dar_shape* s, int T) {
     put(L.vd, B * Hkv * Td * d * 2);
     put(L.nl2, B * Hq * Tr * 4);
     put(L.nd, B * Hq * Tr * 4);
-    put(L.dqr, B * Hq * T * d * 4);
-    put(L.dkr, B * Hkv * T * d * 4);
-    put(L.dvw, B * Hkv * T * d * 4);
-    put(L.dkd, B * Hkv * Td * d * 4);
-    put(L.dvd, B * Hkv * Td * d * 4);
-    L.nchunk = (int)B * ((T + 31) / 32);  // one share per 32 keys of a sequence
+    L.nchunk = (int)B * ((T + 127) / 128);  // one share per workgroup of 128 keys
     put(L.wpart, 2 * Hkv * (size_t)L.nchunk * d * dd * 4);
     L.bytes = off;
     return L;
@@ -1107,11 +1103,6 @@ dar_status dar_attn_prefill_rope_backward(const dar_shape* s, int T, int pos0, c
     a.vd = (const bf16_t*)(wsb + L.vd);
     a.nl2 = (float*)(wsb + L.nl2);
     a.nd = (float*)(wsb + L.nd);
-    a.dqr = (float*)(wsb + L.dqr);
-    a.dkr = (float*)(wsb + L.dkr);
-    a.dvw = (float*)(wsb + L.dvw);
-    a.dkd = (float*)(wsb + L.dkd);
-    a.dvd = (float*)(wsb + L.dvd);
     a.wpart = (float*)(wsb + L.wpart);
     a.dq = (bf16_t*)dq;
     a.dk = (bf16_t*)dk;

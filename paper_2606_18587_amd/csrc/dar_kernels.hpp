@@ -247,15 +247,14 @@ hipError_t launch_bwd_valu(const T* q, const T* k, const T* v, const T* o, const
 // tied), lse (the forward's, natural log), tab [n_pos][r]; qr, kr, kd, vd:
 // the rotary pre-pass of the same inputs (rotated queries and keys, lifted
 // and rotated distant keys and lifted values of positions < T - w).
-// Workspace arrays (fp32): nl2, nd [B*Hq][Tr] (Tr = round_up(T, 64)); dqr
-// [B*Hq][T][d]; dkr, dvw [B*Hkv][T][d]; dkd, dvd [B*Hkv][T - w][d]; wpart
-// [2][Hkv][L.nchunk][d][dd] with L.nchunk = B * ceil(T / 32).
+// Workspace arrays (fp32): nl2, nd [B*Hq][Tr] (Tr = round_up(T, 64)); wpart
+// [2][Hkv][L.nchunk][d][dd] with L.nchunk = B * ceil(T / 128).
 struct RopeBwdArgs {
     const bf16_t *q, *k, *v, *o, *dout, *wd, *wu;
     const float* lse;
     const float* tab;
     const bf16_t *qr, *kr, *kd, *vd;
-    float *nl2, *nd, *dqr, *dkr, *dvw, *dkd, *dvd, *wpart;
+    float *nl2, *nd, *wpart;
     bf16_t *dq, *dk, *dv;
     float *dwd, *dwu;
     BwdWs L;

@@ -134,4 +134,27 @@ __device__ __forceinline__ bf16x8_t lds_tr_operand(const bf16_t* m, int ld, int 
     return __builtin_bit_cast(bf16x8_t, make_uint4(ulo.x, ulo.y, uhi.x, uhi.y));
 }
 
+// lds_tr_operand with the A rows in perm_row order (row R carries column
+// col0 + perm_row(R)): the product's accumulators then hold acc_row order, the
+// B operand layout of a product over those columns.
+__device__ __forceinline__ bf16x8_t lds_tr_operand_perm(const bf16_t* m, int ld, int k0, int col0,
+                                                        int lane) {
+    const int quad = lane >> 4, sl = lane & 15;
+    const int kk = k0 + 8 * (quad >> 1) + (sl >> 2);
+    const int col = col0 + 16 * (quad & 1) + 8 * (sl & 1) + 4 * ((sl >> 1) & 1);
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(m + kk * ld + col));
+    const s16x4_t hi =
+        __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(m + (kk + 4) * ld + col));
+    const uint2 ulo = __builtin_bit_cast(uint2, lo), uhi = __builtin_bit_cast(uint2, hi);
+    return __builtin_bit_cast(bf16x8_t, make_uint4(ulo.x, ulo.y, uhi.x, uhi.y));
+}
+
+// Orders this wavefront's LDS writes before its later LDS reads of other
+// lanes' data (the LDS serves one wavefront's instructions in order; this
+// keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 }  // namespace dar

@@ -96,6 +96,18 @@ def test_other_shapes_and_rotary_dims(d, dd, w, T, r):
     full_compare(di.Workload("rope_bwd_mixed", 52, 2, 4, 1, T, d, dd, w, "bf16"), r, untied=True)
 
 
+@pytest.mark.parametrize("d,dd,w,T,r", [(64, 12, 31, 129, 2), (64, 33, 32, 128, 64),
+                                        (64, 64, 1, 191, 10), (128, 65, 33, 161, 128),
+                                        (128, 73, 0, 127, 34), (128, 33, 130, 131, 48)])
+def test_chain_rule_column_tiles(d, dd, w, T, r):
+    """d_down at the edges of the 32-column tiles up to the largest accepted,
+    rotary dims with and without whole runs of eight, lengths around the
+    workgroup's 128 keys (untied and tied)."""
+    wl = di.Workload("rope_bwd_tiles", 53, 1, 4, 2, T, d, dd, w, "bf16")
+    full_compare(wl, r, untied=True)
+    full_compare(wl, r, pos0=3)
+
+
 def test_offset_positions_and_zero_rotary_dim():
     """Rows at positions 77.. of a longer sequence, and r = 0, whose gradients
     are those of the plain backward (checked against the oracle's)."""
