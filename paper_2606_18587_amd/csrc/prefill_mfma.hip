@@ -784,7 +784,7 @@ void prefill_mfma_kernel(
     const float* __restrict__ knorm, const bf16_t* __restrict__ consts, bf16_t* __restrict__ o,
     float* __restrict__ lse, int Hq, int Hkv, int T, int w, int Tp, int nblk, int BH,
     float c_scale, int q0, int n_rows, int kv0, int Tkv, const bf16_t* __restrict__ wv,
-    const int* __restrict__ seq_lens, LatCache lc) {
+    const int* __restrict__ seq_lens, int parts, LatCache lc) {
     constexpr bool ROPE = MODE == kModeRope;
     constexpr bool CACHE = MODE == kModeDense || MODE == kModePaged;
     constexpr bool PAGED = MODE == kModePaged;
@@ -804,8 +804,10 @@ void prefill_mfma_kernel(
     // [Hkv][DD][D] staged after it
     bf16_t* wV = wv ? wU + DD * LDU : wU;
 
-    // Each workgroup takes row blocks p and nblk-1-p of one (batch, head): a
-    // short and a long causal row block, so every workgroup has the same work.
+    // With two parts a workgroup takes row blocks p and nblk-1-p of one (batch,
+    // head): a short and a long causal row block, so every workgroup has the
+    // same work. With one part (launch_dd: grids that leave the chip room) it
+    // takes block nblk-1-p alone.
     // Workgroups are dealt to the 8 XCDs round-robin; when BH % 8 == 0 all
     // workgroups of a head are placed on one XCD so its L2 holds only the
     // K/V/latents of BH/8 heads.
@@ -835,7 +837,7 @@ void prefill_mfma_kernel(
         const int len_b = sload(lc.lens + b);
         const int nb = lc.n_new ? imin(imax(sload(lc.n_new + b), 0), n_rows) : n_rows;
         if (nb > 0 && (len_b < 0 || len_b + nb > lc.cap)) {
-            for (int part = 0; part < 2; ++part) {
+            for (int part = 0; part < parts; ++part) {
                 const int rb = part == 0 ? nblk - 1 - pair : pair;
                 if (part == 1 && rb >= nblk - 1 - pair) break;
                 for (int idx = tid; idx < BM * D; idx += NW * 64) {
@@ -896,7 +898,7 @@ void prefill_mfma_kernel(
     __syncthreads();
 
 #pragma nounroll
-    for (int part = 0; part < 2; ++part) {
+    for (int part = 0; part < parts; ++part) {
         // Lane-dependent addresses are recomputed for each row block from an
         // opaque copy of the lane id: hoisted out of this loop they would hold
         // (and spill) dozens of registers across both blocks.
@@ -1162,8 +1164,15 @@ static hipError_t launch_dd(int B, int Hq, int Hkv, const PrefillGeo& geo, int w
     constexpr int BM = NW * 32;
     const int T = geo.total();
     const int nblk = (geo.n_rows + BM - 1) / BM;
-    const int npair = (nblk + 1) / 2;
     const int BH = B * Hq;
+    // One row block per workgroup while all of them are resident at once (two
+    // workgroups on each of 256 compute units: LDS and registers): the longest
+    // block is then the whole time, and pairing would put a second block behind
+    // it on a chip that is partly idle (B1 H8 T331 d64 w128, with the pre-pass: 19.4
+    // us as pairs, 17.0 alone). Past that, pairs even out the causal work (B8 H8 T2048 d64 w256 has
+    // 1024 blocks: 44 us as pairs).
+    const int parts = (long long)nblk * BH <= 2 * 256 ? 1 : 2;
+    const int npair = parts == 1 ? nblk : (nblk + 1) / 2;
     const int Tp = ROPE ? round_up(T - w > 0 ? T - w : 0, 32) : prefill_tp(T, w);
     const float c_scale = 1.4426950408889634f / sqrtf((float)D);
     const size_t lds = sizeof(bf16_t) * (4 * 64 * (D + 8) + (wv ? 2 : 1) * DD * (D + 8));
@@ -1176,7 +1185,7 @@ static hipError_t launch_dd(int B, int Hq, int Hkv, const PrefillGeo& geo, int w
                        (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)wd, (const bf16_t*)wu,
                        (const bf16_t*)cK, (const bf16_t*)cVt, cnorm, knorm, (const bf16_t*)consts,
                        (bf16_t*)o, lse, Hq, Hkv, T, w, Tp, nblk, BH, c_scale, geo.q0,
-                       geo.n_rows, geo.kv0, geo.Tkv, (const bf16_t*)wv, geo.seq_lens, lc);
+                       geo.n_rows, geo.kv0, geo.Tkv, (const bf16_t*)wv, geo.seq_lens, parts, lc);
     return hipGetLastError();
 }
 
