@@ -88,21 +88,31 @@ __device__ __forceinline__ bf16x8_t ones3(int hg, int g1) {
                     : zero_bf16x8();
 }
 
-// 8 fp32 values (16-byte aligned) times f, as a bf16 hi + lo pair.
-__device__ __forceinline__ void split_load8(const float* p, float f, bf16x8_t& hi, bf16x8_t& lo) {
-    const float4 a = *reinterpret_cast<const float4*>(p);
-    const float4 b = *reinterpret_cast<const float4*>(p + 4);
+// 8 fp32 values (16-byte aligned).
+struct f32x8 {
+    float4 a, b;
+};
+__device__ __forceinline__ f32x8 load_f8(const float* p) {
+    return f32x8{*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4)};
+}
+__device__ __forceinline__ void add_f8(f32x8& r, const f32x8& x) {
+    r.a.x += x.a.x; r.a.y += x.a.y; r.a.z += x.a.z; r.a.w += x.a.w;
+    r.b.x += x.b.x; r.b.y += x.b.y; r.b.z += x.b.z; r.b.w += x.b.w;
+}
+
+// 8 fp32 values times f, as a bf16 hi + lo pair.
+__device__ __forceinline__ void split_f8(const f32x8& y, float f, bf16x8_t& hi, bf16x8_t& lo) {
     f32x16_t x;
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+    x[0] = y.a.x; x[1] = y.a.y; x[2] = y.a.z; x[3] = y.a.w;
+    x[4] = y.b.x; x[5] = y.b.y; x[6] = y.b.z; x[7] = y.b.w;
     split8(x, 0, f, hi, lo);
 }
 
-// 8 fp32 values (16-byte aligned) times f, as one bf16 operand.
-__device__ __forceinline__ bf16x8_t pack_load8(const float* p, float f) {
-    const float4 a = *reinterpret_cast<const float4*>(p);
-    const float4 b = *reinterpret_cast<const float4*>(p + 4);
-    return __builtin_bit_cast(bf16x8_t, make_uint4(pack2(a.x * f, a.y * f), pack2(a.z * f, a.w * f),
-                                                   pack2(b.x * f, b.y * f), pack2(b.z * f, b.w * f)));
+// 8 fp32 values times f, as one bf16 operand.
+__device__ __forceinline__ bf16x8_t pack_f8(const f32x8& y, float f) {
+    return __builtin_bit_cast(bf16x8_t,
+                              make_uint4(pack2(y.a.x * f, y.a.y * f), pack2(y.a.z * f, y.a.w * f),
+                                         pack2(y.b.x * f, y.b.y * f), pack2(y.b.z * f, y.b.w * f)));
 }
 
 // Workgroup share of a weight gradient: every wavefront adds its C tiles
@@ -569,17 +579,20 @@ __global__ __launch_bounds__(NW * 64) void bwd_rows_dist_kernel(
 // constants) are copied once into LDS for the workgroup, as in the query-side
 // kernel. Each row's -lse and -delta enter through one more product each,
 // the row-constant operand (hi + mid + lo) against ones3. Writes
-// gK = sum dS q~ (q~ unscaled) and gV = sum P dO~ (fp32) of every real key.
-// Grid: ceil(T / (32 NW)) * B * Hkv workgroups (xcd_block_head); key block 0
-// (most rows) first.
+// gK = sum dS q~ (q~ unscaled) and gV = sum P dO~ (fp32) of every real key
+// over the (head, row tile) pairs [pt p, pt p + pt) of part p (bwd_ws_layout)
+// into that part's arrays (a block without distant rows has no part and writes
+// nothing). Grid: np * ceil(T / (32 NW)) * B * Hkv workgroups
+// (xcd_block_head), part 0 first, within a part key block 0 (most rows) first.
 template <int DD, int NW>
 __global__ __launch_bounds__(NW * 64) void bwd_cols_dist_kernel(
     const bf16_t* __restrict__ ckb, const bf16_t* __restrict__ cvb,
     const bf16_t* __restrict__ qts, const bf16_t* __restrict__ qtT,
     const bf16_t* __restrict__ dts, const bf16_t* __restrict__ dtT,
     const bf16_t* __restrict__ rc, float* __restrict__ gk, float* __restrict__ gv, int Hq,
-    int Hkv, int T, int Tr, int w, float gscale, int BKV) {
+    int Hkv, int T, int Tr, int w, float gscale, int BKV, int pt) {
     constexpr int DS = DD / 16, BK = NW * 32;
+    static_assert(BK == 128, "bwd_col_tiles");
     constexpr int NQ = 8 * DD, NT = 256, NC = 128;  // 16-byte chunks per 64-row tile
     constexpr int NCH = 2 * NQ + 2 * NT + NC;
     __shared__ __attribute__((aligned(16))) uint4 tile[NCH];
@@ -591,10 +604,15 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_dist_kernel(
 
     const int tid = lane_id_x(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int cb, bg;
-    xcd_block_head(wg_id_x(), BKV, cb, bg);
+    int cbi, bg;
+    xcd_block_head(wg_id_x(), BKV, cbi, bg);
+    const int nblk = (T + BK - 1) / BK;
+    const int part = cbi / nblk, cb = cbi - part * nblk;
     const int b = bg / Hkv, g = bg % Hkv;
     const int G = Hq / Hkv;
+    const int ntile = bwd_col_tiles(cb, T, w);
+    const int n0 = part * pt, n1 = imin(n0 + pt, G * ntile);
+    if (n0 >= n1) return;  // workgroup-uniform
     const int qc = lane & 31, hg = lane >> 5, prow = perm_row(qc);
     const int cwg = cb * BK;
     const int c0 = cwg + wave * 32, j = c0 + qc;
@@ -644,8 +662,6 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_dist_kernel(
     };
 
     const int t0 = (cwg + w) & ~63;  // first row tile with a distant pair in the workgroup
-    const int ntile = t0 < T ? (T - 1 - t0) / 64 + 1 : 0;
-    const int ntot = G * ntile;
     // two copies per tile (the operand rows and blocks, then the row constants):
     // each keeps at most four loads per thread in registers
     constexpr int NA = NCH - NC;
@@ -660,16 +676,15 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_dist_kernel(
                     reinterpret_cast<const uint4*>(dtT + (bh * T32 + t / 32) * 1024),
                     rcs, NQ, NQ, NT, NT};
     };
-    if (ntot > 0) {  // workgroup-uniform
-    SegRegs<NW, NA> sa = seg_fetch<NW, NA>(segs(0, false), wave, lane);
-    SegRegs<NW, NC> sc = seg_fetch<NW, NC>(segs(0, true), wave, lane);
-    for (int n = 0; n < ntot; ++n) {
+    SegRegs<NW, NA> sa = seg_fetch<NW, NA>(segs(n0, false), wave, lane);
+    SegRegs<NW, NC> sc = seg_fetch<NW, NC>(segs(n0, true), wave, lane);
+    for (int n = n0; n < n1; ++n) {
         const int t = t0 + (n % ntile) * 64;
         __syncthreads();  // the previous tile is no longer read
         seg_store<NW, NA>(sa, tile, wave, lane);
         seg_store<NW, NC>(sc, tile + NA, wave, lane);
         __syncthreads();
-        const int nn = imin(n + 1, ntot - 1);  // the last fetch repeats
+        const int nn = imin(n + 1, n1 - 1);  // the last fetch repeats
         sa = seg_fetch<NW, NA>(segs(nn, false), wave, lane);
         sc = seg_fetch<NW, NC>(segs(nn, true), wave, lane);
         const bool interior = t >= c0 + 31 + w && t + 63 < T;  // every pair distant and real
@@ -680,10 +695,9 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_dist_kernel(
         if (live && !interior && t + 31 >= c0 + w) step(0, t, true);
         if (live && !interior && t + 63 >= c0 + w && t + 32 < T) step(1, t + 32, true);
     }
-    }
     if (!live || j >= T) return;
-    float* gkr = gk + ((size_t)bg * T + j) * DD;
-    float* gvr = gv + ((size_t)bg * T + j) * DD;
+    float* gkr = gk + (((size_t)part * BKV + bg) * T + j) * DD;
+    float* gvr = gv + (((size_t)part * BKV + bg) * T + j) * DD;
 #pragma unroll
     for (int s = 0; s < DS; ++s) {
         const int c = 16 * s + 8 * hg;
@@ -807,7 +821,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_rows_local_kernel(
 #pragma unroll
         for (int s = 0; s < DS; ++s) {
             bf16x8_t hhi, hlo;
-            split_load8(hrow + s * 16 + hg * 8, 1.f, hhi, hlo);
+            split_f8(load_f8(hrow + s * 16 + hg * 8), 1.f, hhi, hlo);
 #pragma unroll
             for (int tt = 0; tt < NT; ++tt) {
                 // A[e][c] = W_up[c][e], rows e = 32 tt + qc, c = 16 s + 8 hg + 0..7
@@ -849,13 +863,12 @@ __global__ __launch_bounds__(NW * 64) void bwd_rows_local_kernel(
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 *reinterpret_cast<bf16x8_t*>(xs + qc * LDK + s * 16 + hg * 8) = pass ? doop[s] : qop[s];
-            const float* yr = pass ? orow : hrow;
             const float f = real ? (pass ? 1.f : scale) : 0.f;  // rows past T add nothing
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 const int c = s * 16 + hg * 8;
                 *reinterpret_cast<bf16x8_t*>(ys + qc * LDH + c) =
-                    (c < DD) ? pack_load8(yr + c, f) : zero_bf16x8();
+                    s < DS ? pack_f8(load_f8((pass ? orow : hrow) + c), f) : zero_bf16x8();
             }
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
@@ -885,7 +898,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_local_kernel(
     const float* __restrict__ gk, const float* __restrict__ gv, const float* __restrict__ nl2,
     const float* __restrict__ nd, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv,
     float* __restrict__ wpart, int Hq, int Hkv, int T, int Tr, int w, float qscale, float scale,
-    int nchunk, int BKV) {
+    int nchunk, int BKV, int pt) {
     constexpr int KS = D / 16, NT = D / 32, DS = DD / 16, BN = 64, LDK = D + 8, LDH = 40;
     constexpr int BK = NW * 32;
     __shared__ __attribute__((aligned(16))) bf16_t lds_qd[2 * BN * LDK];  // Q tile, dO tile
@@ -1002,12 +1015,33 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_local_kernel(
     for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) dkT[tt][r] *= scale;
+    f32x8 ksum[DS], vsum[DS];  // the distant kernel's parts
     if (any_dist) {
+        const int np = (G * bwd_col_tiles(cb, T, w) + pt - 1) / pt;
+        const size_t stride = (size_t)BKV * T * DD;
+#pragma unroll
+        for (int s = 0; s < DS; ++s) {
+            ksum[s] = load_f8(gkr + s * 16 + hg * 8);
+            vsum[s] = load_f8(gvr + s * 16 + hg * 8);
+        }
+        for (int pt_i = 1; pt_i < np; ++pt_i) {  // in part order, one round trip each
+            f32x8 kx[DS], vx[DS];
+#pragma unroll
+            for (int s = 0; s < DS; ++s) {
+                kx[s] = load_f8(gkr + pt_i * stride + s * 16 + hg * 8);
+                vx[s] = load_f8(gvr + pt_i * stride + s * 16 + hg * 8);
+            }
+#pragma unroll
+            for (int s = 0; s < DS; ++s) {
+                add_f8(ksum[s], kx[s]);
+                add_f8(vsum[s], vx[s]);
+            }
+        }
 #pragma unroll
         for (int s = 0; s < DS; ++s) {
             bf16x8_t khi, klo, vhi, vlo;
-            split_load8(gkr + s * 16 + hg * 8, scale, khi, klo);
-            split_load8(gvr + s * 16 + hg * 8, 1.f, vhi, vlo);
+            split_f8(ksum[s], scale, khi, klo);
+            split_f8(vsum[s], 1.f, vhi, vlo);
 #pragma unroll
             for (int tt = 0; tt < NT; ++tt) {
                 const bf16x8_t a = load_bf16x8(wdg + (size_t)(tt * 32 + qc) * DD + s * 16 + hg * 8);
@@ -1044,13 +1078,13 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_local_kernel(
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 *reinterpret_cast<bf16x8_t*>(xs + qc * LDK + s * 16 + hg * 8) = pass ? vop[s] : kop[s];
-            const float* yr = pass ? gvr : gkr;
             const float f = real ? (pass ? 1.f : scale) : 0.f;  // keys past T add nothing
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 const int c = s * 16 + hg * 8;
                 *reinterpret_cast<bf16x8_t*>(ys + qc * LDH + c) =
-                    (c < DD) ? pack_load8(yr + c, f) : zero_bf16x8();
+                    s < DS ? pack_f8(pass ? vsum[imin(s, DS - 1)] : ksum[imin(s, DS - 1)], f)
+                           : zero_bf16x8();
             }
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
@@ -1110,10 +1144,11 @@ static hipError_t launch_bwd_mfma_t(const bf16_t* q, const bf16_t* k, const bf16
                        (const bf16_t*)ckb, (const bf16_t*)ckT, (const bf16_t*)cvb,
                        (const bf16_t*)cvT, (const bf16_t*)qts, (const bf16_t*)dts,
                        (const float*)nl2, (const float*)nd, hk, ol, Hq, Hkv, T, Tr, w, B * Hq);
-    hipLaunchKernelGGL((bwd_cols_dist_kernel<DD, NW>), dim3(nblk * B * Hkv), dim3(NW * 64), 0, st,
-                       (const bf16_t*)ckb, (const bf16_t*)cvb, (const bf16_t*)qts,
+    hipLaunchKernelGGL((bwd_cols_dist_kernel<DD, NW>), dim3(L.np_cols * nblk * B * Hkv), dim3(NW * 64),
+                       0, st, (const bf16_t*)ckb, (const bf16_t*)cvb, (const bf16_t*)qts,
                        (const bf16_t*)qtT, (const bf16_t*)dts, (const bf16_t*)dtT,
-                       (const bf16_t*)rc, gk, gv, Hq, Hkv, T, Tr, w, 1.f / qscale, B * Hkv);
+                       (const bf16_t*)rc, gk, gv, Hq, Hkv, T, Tr, w, 1.f / qscale, B * Hkv,
+                       L.pt_cols);
     hipLaunchKernelGGL((bwd_rows_local_kernel<D, DD, NW>), dim3(nblk * B * Hq), dim3(NW * 64), 0,
                        st, q, k, v, dout, wd, wu, (const float*)hk, (const float*)ol,
                        (const float*)nl2, (const float*)nd, dq, part, Hq, Hkv, T, Tr, w,
@@ -1121,7 +1156,7 @@ static hipError_t launch_bwd_mfma_t(const bf16_t* q, const bf16_t* k, const bf16
     hipLaunchKernelGGL((bwd_cols_local_kernel<D, DD, NW>), dim3(nblk * B * Hkv), dim3(NW * 64), 0,
                        st, q, k, v, dout, wd, (const float*)gk, (const float*)gv,
                        (const float*)nl2, (const float*)nd, dk, dv, part, Hq, Hkv, T, Tr, w,
-                       qscale, scale, L.nchunk, B * Hkv);
+                       qscale, scale, L.nchunk, B * Hkv, L.pt_cols);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_bwd_wreduce(part, dwd, dwu, Hkv, D, DD, L, st);

@@ -410,8 +410,8 @@ dar_status dar_attn_prefill_rope(const dar_shape* s, int T, int pos0, const dar_
 size_t dar_prefill_backward_workspace_bytes(const dar_shape* s, int T) {
     if (check_shape(s) != DAR_OK || T < 1) return 0;
     // enough for either kernel family (DAR_BWD_VALU may pick the generic one)
-    const size_t a = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, false).bytes;
-    const size_t b = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, true).bytes;
+    const size_t a = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, s->w, false).bytes;
+    const size_t b = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, s->w, true).bytes;
     return a > b ? a : b;
 }
 
@@ -499,7 +499,7 @@ dar_status dar_attn_prefill_backward(const dar_shape* s, int T, const void* q, c
     hipError_t e;
     const bool fast = bwd_mfma_supported(s->d, s->d_down, s->dtype == DAR_BF16) &&
                       !env_flag("DAR_BWD_VALU");
-    const BwdWs L = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, fast);
+    const BwdWs L = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, s->w, fast);
     if (fast)
         e = launch_bwd_mfma((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)o,
                             lse, (const bf16_t*)dout, (const bf16_t*)w_down, (const bf16_t*)w_up,

@@ -1168,9 +1168,9 @@ static hipError_t launch_dd(int B, int Hq, int Hkv, const PrefillGeo& geo, int w
     // One row block per workgroup while all of them are resident at once (two
     // workgroups on each of 256 compute units: LDS and registers): the longest
     // block is then the whole time, and pairing would put a second block behind
-    // it on a chip that is partly idle (B1 H8 T331 d64 w128, with the pre-pass: 19.4
-    // us as pairs, 17.0 alone). Past that, pairs even out the causal work (B8 H8 T2048 d64 w256 has
-    // 1024 blocks: 44 us as pairs).
+    // it on a chip that is partly idle (B1 H8 T331 d64 w128, with the
+    // pre-pass: 19.4 us as pairs, 17.0 alone). Past that, pairs even out the
+    // causal work (B8 H8 T2048 d64 w256 has 1024 blocks: 44 us as pairs).
     const int parts = (long long)nblk * BH <= 2 * 256 ? 1 : 2;
     const int npair = parts == 1 ? nblk : (nblk + 1) / 2;
     const int Tp = ROPE ? round_up(T - w > 0 ? T - w : 0, 32) : prefill_tp(T, w);

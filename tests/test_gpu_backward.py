@@ -165,3 +165,15 @@ def test_deterministic():
     b = run_gpu(inp, wl.w)
     for x, y in zip(a, b):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("G,T,w", [(8, 700, 64), (8, 641, 1), (4, 1025, 300), (1, 1217, 65)])
+def test_distant_parts(G, T, w, monkeypatch):
+    """Key blocks whose distant rows are cut into several parts (more than 8
+    tiles of 64 rows over the group's heads), partly filled last parts, and
+    blocks with none. A weight gradient's small entries carry the rounding of
+    all G T summands, which grows as their square root: ELEM_BOUND's figure is
+    for the 600 rows a KV head has in the cases above."""
+    for n in ("dwd", "dwu"):
+        monkeypatch.setitem(ELEM_BOUND, n, 12.0 * max(1.0, (G * T / 600.0) ** 0.5))
+    full_compare(di.Workload("bf16_parts", 15, 1, G, 1, T, 64, 16, w, "bf16"), untied=(T % 2 == 1))
