@@ -18,7 +18,7 @@ LIB = os.path.join(PKG, "libdar.so")
 K0_LIB = os.path.join(PKG, "libdar_k0.so")
 K0_SOURCE = "k0_microbench.hip"
 SOURCES = ["dar_api.hip", "latent.hip", "prefill_valu.hip", "prefill_mfma.hip", "decode.hip",
-           "decode_mfma.hip", "backward.hip", "backward_mfma.hip", "rope.hip"]
+           "decode_mfma.hip", "f32_mfma.hip", "backward.hip", "backward_mfma.hip", "rope.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [

@@ -160,6 +160,11 @@ hipError_t run_prefill(const dar_shape* s, const PrefillGeo& geo, const void* q,
                                      (float*)cK, (float*)cV, cnorm, knorm, (float*)consts, s->B,
                                      s->Hkv, geo, s->d, s->d_down, s->w, false, stream);
     if (e != hipSuccess) return e;
+    if (f32_mfma_supported(s->d, s->d_down))
+        return launch_prefill_f32((const float*)q, (const float*)k, (const float*)v,
+                                  (const float*)w_down, (const float*)w_up, (const float*)cK,
+                                  (const float*)cV, (float*)o, lse, s->B, s->Hq, s->Hkv, geo, s->d,
+                                  s->d_down, s->w, stream, (const float*)w_val);
     return launch_prefill_valu<float>((const float*)q, (const float*)k, (const float*)v,
                                       (const float*)w_down, (const float*)w_up, (const float*)cK,
                                       (const float*)cV, (float*)o, lse, s->B, s->Hq, s->Hkv, geo,
@@ -511,6 +516,11 @@ dar_status dar_attn_prefill_backward(const dar_shape* s, int T, const void* q, c
                                     (const bf16_t*)w_up, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv,
                                     dw_down, dw_up, (char*)ws, L, s->B, s->Hq, s->Hkv, T, s->d,
                                     s->d_down, s->w, stream);
+    else if (f32_mfma_supported(s->d, s->d_down) && !env_flag("DAR_BWD_VALU"))
+        e = launch_bwd_f32((const float*)q, (const float*)k, (const float*)v, (const float*)o, lse,
+                           (const float*)dout, (const float*)w_down, (const float*)w_up, (float*)dq,
+                           (float*)dk, (float*)dv, dw_down, dw_up, (char*)ws, L, s->B, s->Hq,
+                           s->Hkv, T, s->d, s->d_down, s->w, stream);
     else
         e = launch_bwd_valu<float>((const float*)q, (const float*)k, (const float*)v,
                                    (const float*)o, lse, (const float*)dout, (const float*)w_down,

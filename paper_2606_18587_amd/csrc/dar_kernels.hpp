@@ -218,9 +218,11 @@ __host__ __device__ inline int bwd_col_tiles(int blk, int T, int w) {
     const long long t0 = ((long long)128 * blk + w) & ~63LL;
     return t0 < T ? (int)((T - 1 - t0) / 64) + 1 : 0;
 }
-// Row chunks of the weight-gradient reduction: about 256 rows each, at most 128.
+// Row chunks of the weight-gradient reduction: about 16 rows each, at most 128
+// (with 256 rows each, B1 H8 T331 d64 had 32 workgroups of one row at a time:
+// 183 of the training step's 605 us).
 static inline int bwd_nchunk(long long rows) {
-    long long n = (rows + 255) / 256;
+    long long n = (rows + 15) / 16;
     return (int)(n < 1 ? 1 : (n > 128 ? 128 : n));
 }
 // mfma: chunks of the weight-gradient shares are the matrix-core kernels'
@@ -239,6 +241,18 @@ hipError_t launch_bwd_weights(const T* q, const T* k, const T* v, const T* dout,
                               const float* gv, const float* hk, const float* ol, float* part,
                               float* dwd, float* dwu, int B, int Hq, int Hkv, int T_, int d,
                               int dd, const BwdWs& L, hipStream_t st);
+// fp32 prefill and backward on the fp32 matrix cores (f32_mfma.hip), d <= 128;
+// arguments and workspace as the vector-ALU kernels.
+bool f32_mfma_supported(int d, int dd);
+hipError_t launch_prefill_f32(const float* q, const float* k, const float* v, const float* wd,
+                              const float* wu, const float* cK, const float* cVt, float* o,
+                              float* lse, int B, int Hq, int Hkv, const PrefillGeo& geo, int d,
+                              int dd, int w, hipStream_t st, const float* wv);
+hipError_t launch_bwd_f32(const float* q, const float* k, const float* v, const float* o,
+                          const float* lse, const float* dout, const float* wd, const float* wu,
+                          float* dq, float* dk, float* dv, float* dwd, float* dwu, char* ws,
+                          const BwdWs& L, int B, int Hq, int Hkv, int T, int d, int dd, int w,
+                          hipStream_t st);
 // Matrix-core backward (bf16, d in {64, 128}, d_down in {16, 32}).
 bool bwd_mfma_supported(int d, int dd, bool bf16);
 hipError_t launch_bwd_mfma(const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* o,

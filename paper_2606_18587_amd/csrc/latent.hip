@@ -16,6 +16,9 @@
 
 namespace dar {
 
+// Rows of W_down that fit beside the tokens in LDS (d = 256 would take 164 KB).
+constexpr int kLatentWRows = 128;
+
 // One block = 64 tokens of one (batch, KV head). Lane = token; the 4 waves
 // share the 2*dd output columns (K and V) in chunks of 8.
 //   cK:  [B*Hkv][Tp][dd]               token-major (columns in latent_pos order
@@ -28,11 +31,12 @@ __global__ __launch_bounds__(256) void prefill_latent_kernel(
     T* __restrict__ cK, T* __restrict__ cVt, int Hkv, int d, int dd, int Tl, int Tp, int perm,
     int kv0, int Tkv, int lat0, const T* __restrict__ k_lat, const T* __restrict__ v_lat,
     int cap) {
-    extern __shared__ float xs[];  // [2][64][d+1]
+    extern __shared__ __align__(16) float xs[];  // [2][64][d+1], then the wavefronts' W_down chunks
     const int bg = wg_id_y();
     const int g = bg % Hkv;
     const int t0 = wg_id_x() * 64;
     const int ld = d + 1;
+    float* ws = xs + 2 * 64 * ld;  // [4][kLatentWRows][8]
     const T* wdg = wd + (size_t)g * d * dd;
     // rows of the positions whose latent is projected here (k/v row = position - kv0)
     for (int which = 0; which < 2; ++which) {
@@ -57,12 +61,41 @@ __global__ __launch_bounds__(256) void prefill_latent_kernel(
         float acc[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-        for (int e = 0; e < d; ++e) {
-            const float xv = xr[e];
+        if (d <= kLatentWRows) {
+            // the chunk's eight columns of W_down through the wavefront's LDS
+            // rows, zero padded (read from global memory inside the loop, each
+            // element waited for its eight scalar loads: 32 us at B1 H8
+            // T331 d64 d_down16 fp32, 15 us so)
+            float* wr = ws + wave * kLatentWRows * 8;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int idx = lane; idx < 8 * d; idx += 64) {
+                const int e = idx >> 3, j = idx & 7;
+                wr[idx] = c0 + j < dd ? elem<T>::load(wdg + (size_t)e * dd + c0 + j) : 0.f;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+            for (int e = 0; e < d; ++e) {
+                const float xv = xr[e];
+                const float4 wa = *reinterpret_cast<const float4*>(wr + 8 * e);
+                const float4 wb = *reinterpret_cast<const float4*>(wr + 8 * e + 4);
+                acc[0] = __builtin_fmaf(xv, wa.x, acc[0]);
+                acc[1] = __builtin_fmaf(xv, wa.y, acc[1]);
+                acc[2] = __builtin_fmaf(xv, wa.z, acc[2]);
+                acc[3] = __builtin_fmaf(xv, wa.w, acc[3]);
+                acc[4] = __builtin_fmaf(xv, wb.x, acc[4]);
+                acc[5] = __builtin_fmaf(xv, wb.y, acc[5]);
+                acc[6] = __builtin_fmaf(xv, wb.z, acc[6]);
+                acc[7] = __builtin_fmaf(xv, wb.w, acc[7]);
+            }
+        } else {
+            for (int e = 0; e < d; ++e) {
+                const float xv = xr[e];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (c0 + j < dd)
-                    acc[j] = __builtin_fmaf(xv, elem<T>::load(wdg + (size_t)e * dd + c0 + j), acc[j]);
+                for (int j = 0; j < 8; ++j)
+                    if (c0 + j < dd)
+                        acc[j] = __builtin_fmaf(xv, elem<T>::load(wdg + (size_t)e * dd + c0 + j), acc[j]);
+            }
         }
         if (t < Tp) {
             // positions below lat0: the cache's latent, copied
@@ -484,7 +517,7 @@ static hipError_t launch_prefill_latent_valu(const T* k, const T* v, const T* wd
     if (Tl <= 0) return hipSuccess;
     const int Tp = prefill_tp(T_, w);
     dim3 grid((Tp + 63) / 64, B * Hkv);
-    const size_t lds = sizeof(float) * 2 * 64 * (d + 1);
+    const size_t lds = sizeof(float) * (2 * 64 * (d + 1) + (d <= kLatentWRows ? 4 * kLatentWRows * 8 : 0));
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)prefill_latent_kernel<T>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
