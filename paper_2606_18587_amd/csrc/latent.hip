@@ -448,6 +448,56 @@ __global__ __launch_bounds__(256) void prefill_latent_mfma_kernel(
     }
 }
 
+// One new token per lane column (both lane halves) of a matrix-core append: the
+// leaving rows rk, rv (project) are projected into ok, ov, the new rows nk, nv
+// (to_ring) go to the ring rows dk, dv. All rows are requested before any is
+// used or stored (keys, then values, each after the other's stores, a
+// one-token append was a chain of five memory round trips: 7.3 us at B4 Hkv8
+// in pages, 5.9 so), and a ring
+// slot is read before it is rewritten by the same lane. Row pointers are valid
+// whatever the flags.
+template <int D>
+__device__ __forceinline__ void append_token(const lbf16x8 (&wa)[D / 16], const bf16_t* rk,
+                                             const bf16_t* rv, const bf16_t* nk, const bf16_t* nv,
+                                             bf16_t* ok, bf16_t* ov, bf16_t* dk, bf16_t* dv, int dd,
+                                             int hg, bool project, bool any_project, bool to_ring) {
+    constexpr int KS = D / 16;
+    lbf16x8 xk[KS], xv[KS], yk[KS], yv[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        yk[s] = lload8(nk + s * 16 + hg * 8);
+        yv[s] = lload8(nv + s * 16 + hg * 8);
+    }
+    if (any_project) {  // uniform
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            xk[s] = lload8(rk + s * 16 + hg * 8);
+            xv[s] = lload8(rv + s * 16 + hg * 8);
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            if (!project) xk[s] = xv[s] = __builtin_bit_cast(lbf16x8, make_uint4(0, 0, 0, 0));
+        const lf32x16 ak = project_mfma<D>(wa, xk), av = project_mfma<D>(wa, xv);
+        if (project) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int c = acc_col(r, hg);
+                if (c < dd) {
+                    ok[c] = f32_to_bf16(ak[r]);
+                    ov[c] = f32_to_bf16(av[r]);
+                }
+            }
+        }
+    }
+    if (to_ring) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            *reinterpret_cast<lbf16x8*>(dk + s * 16 + hg * 8) = yk[s];
+            *reinterpret_cast<lbf16x8*>(dv + s * 16 + hg * 8) = yv[s];
+        }
+    }
+}
+
 // Cache append for bf16 with the matrix-core projection. One wavefront per 32
 // new tokens of one (batch, KV head); modes as in append_kernel. The lane that
 // reads elements [16s + 8hg, +8) of the token leaving ring slot p % w is the
@@ -470,36 +520,15 @@ __global__ __launch_bounds__(64) void append_mfma_kernel(
     const bool to_ring = mode != 1 && valid && w > 0 && tt >= n - w;
     lbf16x8 wa[KS];
     if (mode != 2) load_wd_operand<D>(wd + (size_t)g * D * dd, dd, lane, wa);
-    for (int which = 0; which < 2; ++which) {
-        const bf16_t* src_new = (which ? v_new : k_new) + (size_t)bg * n * D;
-        bf16_t* ring = (which ? v_win : k_win) + (size_t)bg * w * D;
-        if (mode != 2) {
-            const bf16_t* row = src_new;
-            if (project) row = (ex < len) ? ring + (size_t)(ex % w) * D : src_new + (size_t)(ex - len) * D;
-            lbf16x8 x[KS];
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                x[s] = lload8(row + s * 16 + hg * 8);
-                if (!project) x[s] = __builtin_bit_cast(lbf16x8, make_uint4(0, 0, 0, 0));
-            }
-            const lf32x16 acc = project_mfma<D>(wa, x);
-            if (project) {
-                bf16_t* out = (which ? v_lat : k_lat) + ((size_t)bg * cap + ex) * dd;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int c = acc_col(r, hg);
-                    if (c < dd) out[c] = f32_to_bf16(acc[r]);
-                }
-            }
-        }
-        if (to_ring) {
-            const bf16_t* src = src_new + (size_t)tt * D;
-            bf16_t* dst = ring + (size_t)((len + tt) % w) * D;
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                *reinterpret_cast<uint4*>(dst + s * 16 + hg * 8) = *reinterpret_cast<const uint4*>(src + s * 16 + hg * 8);
-        }
-    }
+    const size_t new0 = (size_t)bg * n, ring0 = (size_t)bg * w;
+    const bool old = project && ex < len;  // the leaving token is in the ring
+    const size_t row = old ? (ring0 + ex % w) * D : (new0 + (project ? ex - len : 0)) * D;
+    const size_t src = (new0 + (to_ring ? tt : 0)) * D;
+    const size_t dst = to_ring ? (ring0 + (len + tt) % w) * D : 0;
+    const size_t out = project ? ((size_t)bg * cap + ex) * dd : 0;
+    append_token<D>(wa, (old ? k_win : k_new) + row, (old ? v_win : v_new) + row, k_new + src,
+                    v_new + src, k_lat + out, v_lat + out, k_win + dst, v_win + dst, dd, hg, project,
+                    mode != 2, to_ring);
 }
 
 // The matrix-core projection is used exactly on the shapes the matrix-core
@@ -737,39 +766,23 @@ __global__ __launch_bounds__(64) void append_paged_mfma_kernel(
     const int b = bg / Hkv, g = bg - (bg / Hkv) * Hkv;
     const int lane = lane_id_x();
     const int tl = lane & 31, hg = lane >> 5;
+    lbf16x8 wa[KS];
+    load_wd_operand<D>(wd + (size_t)g * D * dd, dd, lane, wa);
     const int len = pg.lens[b];
     if (len < 0 || len >= pg.maxb * pg.ps) return;  // overflowed, or at capacity: nothing stored
     const int ex = len - w;
     int page = -1;
     if (ex >= 0) page = pg.bt[(size_t)b * pg.maxb + ex / pg.ps];
     const bool project = ex >= 0 && page >= 0 && page < pg.n_pages;
-    lbf16x8 wa[KS];
-    load_wd_operand<D>(wd + (size_t)g * D * dd, dd, lane, wa);
-    for (int which = 0; which < 2; ++which) {
-        const bf16_t* src_new = (which ? v_new : k_new) + (size_t)bg * D;
-        bf16_t* ring = (which ? v_win : k_win) + (size_t)bg * w * D;
-        const bf16_t* row = w > 0 ? ring + (size_t)(imax(ex, 0) % w) * D : src_new;
-        lbf16x8 x[KS];
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-            x[s] = (project && tl == 0) ? lload8(row + s * 16 + hg * 8)
-                                        : __builtin_bit_cast(lbf16x8, make_uint4(0, 0, 0, 0));
-        const lf32x16 acc = project_mfma<D>(wa, x);
-        if (project && tl == 0) {
-            bf16_t* out = (which ? v_pool : k_pool) + (((size_t)page * Hkv + g) * pg.ps + ex % pg.ps) * dd;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int c = acc_col(r, hg);
-                if (c < dd) out[c] = f32_to_bf16(acc[r]);
-            }
-        }
-        if (w > 0 && tl == 0) {
-            bf16_t* dst = ring + (size_t)(len % w) * D;
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                *reinterpret_cast<uint4*>(dst + s * 16 + hg * 8) = *reinterpret_cast<const uint4*>(src_new + s * 16 + hg * 8);
-        }
-    }
+    // (column 0 carries the token; the others' rows are loaded and dropped)
+    const size_t src = (size_t)bg * D;
+    const bool old = w > 0 && ex >= 0;  // the leaving token is in the ring
+    const size_t row = old ? ((size_t)bg * w + ex % w) * D : src;
+    const size_t dst = w > 0 ? ((size_t)bg * w + len % w) * D : 0;
+    const size_t out = project ? (((size_t)page * Hkv + g) * pg.ps + ex % pg.ps) * dd : 0;
+    append_token<D>(wa, (old ? k_win : k_new) + row, (old ? v_win : v_new) + row, k_new + src,
+                    v_new + src, k_pool + out, v_pool + out, k_win + dst, v_win + dst, dd, hg,
+                    project && tl == 0, project, w > 0 && tl == 0);
 }
 
 // The same for every dtype and head size, on the vector ALUs (project_col:
@@ -1035,37 +1048,15 @@ __global__ __launch_bounds__(64) void append_chunk_paged_mfma_kernel(
     const bool to_ring = mode != 1 && valid && w > 0 && tt >= nb - w;
     lbf16x8 wa[KS];
     if (mode != 2) load_wd_operand<D>(wd + (size_t)g * D * dd, dd, lane, wa);
-    for (int which = 0; which < 2; ++which) {
-        const bf16_t* src_new = (which ? v_new : k_new) + (size_t)bg * n * D;
-        bf16_t* ring = (which ? v_win : k_win) + (size_t)bg * w * D;
-        if (mode != 2) {
-            const bf16_t* row = src_new;
-            if (project) row = (ex < L) ? ring + (size_t)(ex % w) * D : src_new + (size_t)(ex - L) * D;
-            lbf16x8 x[KS];
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                x[s] = lload8(row + s * 16 + hg * 8);
-                if (!project) x[s] = __builtin_bit_cast(lbf16x8, make_uint4(0, 0, 0, 0));
-            }
-            const lf32x16 acc = project_mfma<D>(wa, x);
-            if (project) {
-                bf16_t* out = (which ? v_pool : k_pool) +
-                              (((((size_t)page) * Hkv + g) << lc.ps_shift) + (ex & ((1 << lc.ps_shift) - 1))) * dd;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int c = acc_col(r, hg);
-                    if (c < dd) out[c] = f32_to_bf16(acc[r]);
-                }
-            }
-        }
-        if (to_ring) {
-            const bf16_t* src = src_new + (size_t)tt * D;
-            bf16_t* dst = ring + (size_t)((L + tt) % w) * D;
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                *reinterpret_cast<uint4*>(dst + s * 16 + hg * 8) = *reinterpret_cast<const uint4*>(src + s * 16 + hg * 8);
-        }
-    }
+    const size_t new0 = (size_t)bg * n, ring0 = (size_t)bg * w;
+    const bool old = project && ex < L;  // the leaving token is in the ring
+    const size_t row = old ? (ring0 + ex % w) * D : (new0 + (project ? ex - L : 0)) * D;
+    const size_t src = (new0 + (to_ring ? tt : 0)) * D;
+    const size_t dst = to_ring ? (ring0 + (L + tt) % w) * D : 0;
+    const size_t out = project ? (((((size_t)page) * Hkv + g) << lc.ps_shift) + (ex & ((1 << lc.ps_shift) - 1))) * dd : 0;
+    append_token<D>(wa, (old ? k_win : k_new) + row, (old ? v_win : v_new) + row, k_new + src,
+                    v_new + src, k_pool + out, v_pool + out, k_win + dst, v_win + dst, dd, hg, project,
+                    mode != 2, to_ring);
 }
 
 hipError_t launch_append_chunk_paged(const bf16_t* k_new, const bf16_t* v_new, const bf16_t* wd,
