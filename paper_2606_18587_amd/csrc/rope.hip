@@ -185,6 +185,15 @@ __global__ __launch_bounds__(256) void rope_lift_kernel(const T* __restrict__ k,
 // per 8-element chunk; a rotated chunk is combined with its partner chunk
 // (r / 16 chunks away) element by element.
 
+typedef __bf16 rbf16x2 __attribute__((ext_vector_type(2)));
+typedef float rf32x2 __attribute__((ext_vector_type(2)));
+
+// Two fp32 values as a bf16 pair, rounded to nearest even.
+__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
+    rf32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, rbf16x2));
+}
+
 template <typename T> struct vec8;
 template <> struct vec8<bf16_t> {
     static __device__ __forceinline__ void load(const bf16_t* p, float (&x)[8]) {
@@ -200,11 +209,13 @@ template <> struct vec8<bf16_t> {
     static __device__ __forceinline__ float store(bf16_t* p, const float (&y)[8]) {
         uint32_t w4[4];
         float sq = 0.f;
+        // (the packed conversion, one instruction a pair: rounded by hand, seven
+        // a value, the stores were the longest part of the lift: 18.9 -> 17.1 us
+        // at B4 H16 T2048 d64 d_down16 w512)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const bf16_t a = f32_to_bf16(y[2 * j]), b = f32_to_bf16(y[2 * j + 1]);
-            w4[j] = (uint32_t)a | ((uint32_t)b << 16);
-            const float fa = bf16_to_f32(a), fb = bf16_to_f32(b);
+            w4[j] = pack_bf16x2(y[2 * j], y[2 * j + 1]);
+            const float fa = __uint_as_float(w4[j] << 16), fb = __uint_as_float(w4[j] & 0xffff0000u);
             sq = __builtin_fmaf(fa, fa, __builtin_fmaf(fb, fb, sq));
         }
         *reinterpret_cast<uint4*>(p) = make_uint4(w4[0], w4[1], w4[2], w4[3]);
@@ -257,26 +268,33 @@ __device__ __forceinline__ float chunk_row_sum(float x, int nch) {
 }
 
 // Qr / Kr rows (vectorised): grid (ceil(T/32), n_seq), 32 * d/8 threads.
+// Sequences from n_x on are those of a second array, x2 -> out2, with the block
+// norms (queries and keys in one launch).
 template <typename T>
 __global__ __launch_bounds__(1024) void rope_rows_vec_kernel(const T* __restrict__ x, T* __restrict__ out,
-                                                             float* __restrict__ norm,
+                                                             const T* __restrict__ x2,
+                                                             T* __restrict__ out2, int n_x,
+                                                             float* __restrict__ norm2,
                                                              const float* __restrict__ tab, int T_,
                                                              int d, int r, int pos0) {
     __shared__ float rsq[32];
     const int nch = d >> 3;
     const int tid = lane_id_x();
     const int row = tid / nch, ch = tid - (tid / nch) * nch;
-    const int blk = wg_id_x(), seq = wg_id_y();
+    const int blk = wg_id_x();
+    const bool second = wg_id_y() >= n_x;
+    const int seq = second ? wg_id_y() - n_x : wg_id_y();
     const int t = blk * 32 + row;
+    float* const norm = second ? norm2 : nullptr;
     float sq = 0.f;
     if (t < T_) {
-        const T* xr = x + ((size_t)seq * T_ + t) * d;
+        const T* xr = (second ? x2 : x) + ((size_t)seq * T_ + t) * d;
         const int hc = r >> 4;
         float a[8], b[8], y[8];
         vec8<T>::load(xr + ch * 8, a);
         if (ch < 2 * hc) vec8<T>::load(xr + (ch < hc ? ch + hc : ch - hc) * 8, b);
         rotate_chunk(ch, r, a, b, tab + (size_t)(pos0 + t) * r, y);
-        sq = vec8<T>::store(out + ((size_t)seq * T_ + t) * d + ch * 8, y);
+        sq = vec8<T>::store((second ? out2 : out) + ((size_t)seq * T_ + t) * d + ch * 8, y);
     }
     if (norm) {
         sq = chunk_row_sum(sq, nch);
@@ -396,16 +414,9 @@ __global__ __launch_bounds__(256) void rope_lift_lds_kernel(const T* __restrict_
 
 typedef __bf16 rbf16x8 __attribute__((ext_vector_type(8)));
 typedef float rf32x16 __attribute__((ext_vector_type(16)));
-typedef float rf32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 rbf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ rf32x16 rmfma(rbf16x8 a, rbf16x8 b, rf32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ uint32_t rpack2(float a, float b) {
-    rf32x2 v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, rbf16x2));
 }
 
 template <int D, int DD>
@@ -464,8 +475,8 @@ __global__ __launch_bounds__(256) void rope_lift_mfma_kernel(const bf16_t* __res
         rbf16x8 cb[DS];
 #pragma unroll
         for (int s2 = 0; s2 < DS; ++s2)
-            cb[s2] = __builtin_bit_cast(rbf16x8, make_uint4(rpack2(c[8 * s2 + 0], c[8 * s2 + 1]), rpack2(c[8 * s2 + 2], c[8 * s2 + 3]),
-                                                            rpack2(c[8 * s2 + 4], c[8 * s2 + 5]), rpack2(c[8 * s2 + 6], c[8 * s2 + 7])));
+            cb[s2] = __builtin_bit_cast(rbf16x8, make_uint4(pack_bf16x2(c[8 * s2 + 0], c[8 * s2 + 1]), pack_bf16x2(c[8 * s2 + 2], c[8 * s2 + 3]),
+                                                            pack_bf16x2(c[8 * s2 + 4], c[8 * s2 + 5]), pack_bf16x2(c[8 * s2 + 6], c[8 * s2 + 7])));
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             rf32x16 x = {};
@@ -522,10 +533,16 @@ hipError_t launch_rope_prepass(const T* q, const T* k, const T* v, const T* wd, 
     const bool vec = rope_vec_ok(d, r);
     if (vec) {
         const int nt = 32 * (d / 8);
-        hipLaunchKernelGGL(rope_rows_vec_kernel<T>, dim3(nb, B * Hq), dim3(nt), 0, st, q, qr,
-                           (float*)nullptr, tab, T_, d, r, pos0);
-        hipLaunchKernelGGL(rope_rows_vec_kernel<T>, dim3(nb, B * Hkv), dim3(nt), 0, st, k, kr, knorm,
-                           tab, T_, d, r, pos0);
+        // (grid y: B Hq + B Hkv, each at most 65535 for the two launches before)
+        if ((long long)B * (Hq + Hkv) <= 65535) {
+            hipLaunchKernelGGL(rope_rows_vec_kernel<T>, dim3(nb, B * (Hq + Hkv)), dim3(nt), 0, st, q, qr,
+                               k, kr, B * Hq, knorm, tab, T_, d, r, pos0);
+        } else {
+            hipLaunchKernelGGL(rope_rows_vec_kernel<T>, dim3(nb, B * Hq), dim3(nt), 0, st, q, qr, k, kr,
+                               B * Hq, (float*)nullptr, tab, T_, d, r, pos0);
+            hipLaunchKernelGGL(rope_rows_vec_kernel<T>, dim3(nb, B * Hkv), dim3(nt), 0, st, q, qr, k, kr,
+                               0, knorm, tab, T_, d, r, pos0);
+        }
     } else {
         hipLaunchKernelGGL(rope_rows_kernel<T>, dim3(nb, B * Hq), dim3(256), 0, st, q, qr,
                            (float*)nullptr, tab, T_, d, r, pos0);
@@ -777,9 +794,9 @@ hipError_t launch_rope_chunk_prepass(const T* q, const T* ctx_k, const T* ctx_v,
     const int lat0 = len - w > 0 ? len - w : 0;  // cached latents: positions < lat0
     const int nt = 32 * (d / 8);
     hipLaunchKernelGGL(rope_rows_vec_kernel<T>, dim3((n + 31) / 32, B * Hq), dim3(nt), 0, st, q, qr,
-                       (float*)nullptr, tab, n, d, r, len);
+                       (const T*)nullptr, (T*)nullptr, B * Hq, (float*)nullptr, tab, n, d, r, len);
     hipLaunchKernelGGL(rope_rows_vec_kernel<T>, dim3((Tc + 31) / 32, B * Hkv), dim3(nt), 0, st, ctx_k,
-                       kr, (float*)nullptr, tab, Tc, d, r, kv0);
+                       kr, (const T*)nullptr, (T*)nullptr, B * Hkv, (float*)nullptr, tab, Tc, d, r, kv0);
     const int nkb = (T_ + 31) / 32;
     hipLaunchKernelGGL(block_norm_kernel<T>, dim3(nkb - (kv0 >> 5), B * Hkv), dim3(256), 0, st,
                        (const T*)kr, Tc, kv0, Tc, d, knorm, nkb);

@@ -26,3 +26,20 @@ def test_row_blocks_alone_and_in_pairs(B, H, T):
         ref = oracle.rows(inp["k"].f64[b, h], inp["v"].f64[b, h], inp["wd"].f64[h], None, wl.w,
                           list(range(T)), inp["q"].f64[b, h])
         assert np.abs(o[b, h] - ref).max() <= tol("bf16"), (b, h)
+
+
+def test_rotary_rows_in_one_or_two_launches():
+    """Queries and keys are rotated in one launch while their heads fit its
+    grid (65535): past that, in two; the same rows come out either way."""
+    H, T, d, dd = 33000, 2, 64, 16
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn(1, H, T, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    wd = (torch.randn(H, d, dd, generator=g, device="cuda") / 8).to(torch.bfloat16)
+    rope = dar.Rope(16, n_pos=T)
+    o = dar.dar_attn_prefill_rope(q, k, v, wd, None, 1, rope)
+    n = 200
+    for h in (0, 16000, H - n):
+        s = slice(h, h + n)
+        part = dar.dar_attn_prefill_rope(*(x[:, s].contiguous() for x in (q, k, v)), wd[s].contiguous(),
+                                         None, 1, rope)
+        assert torch.equal(o[:, s].view(torch.int16), part.view(torch.int16)), h
