@@ -39,36 +39,9 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 }
 
-BwdWs bwd_ws_layout(int B, int Hq, int Hkv, int T, int d, int dd, int w, bool mfma) {
+BwdWs bwd_ws_layout(int B, int Hq, int Hkv, int T, int d, int dd, bool mfma) {
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     BwdWs L{};
-    L.np_cols = 1;
-    if (mfma) {
-        // The key-side distant kernel has few, long blocks when several query
-        // heads share a KV head, and its causal blocks differ in length by the
-        // whole sequence: the first one is the time (B2 Hq16 Hkv4 T4001 d128
-        // d_down32 w512: 256 blocks). A block's (head, row tile) pairs are cut
-        // into parts of about one of kSlots equal shares of the whole work, at
-        // least 8 tiles each (a part costs about two tiles to start and
-        // finish), each with its own fp32 sums, which the window kernel adds in
-        // part order: 267 -> 114 us there, the whole training step 717 -> 560 us
-        // (572 with 768 slots, 561 with 512). With a block for every resident
-        // workgroup already (four on each of 256 compute units) the parts only
-        // add their sums (B8 H8 T2048 d64 w256, 1024 blocks: 38 against 43 us in
-        // the kernel, 239.4 against 238.0 in the step), so there is one.
-        // The query side has a block per query head and gains nothing from the
-        // same cut (83 against 81 us there, 36.8 against 38.3 us at B8 H8 T2048
-        // d64 w256).
-        constexpr long long kSlots = 1280;
-        const int nblk = (T + 127) / 128;
-        long long cols = 0;
-        for (int i = 0; i < nblk; ++i) cols += (long long)bwd_col_tiles(i, T, w) * (Hq / Hkv);
-        const long long most = (long long)bwd_col_tiles(0, T, w) * (Hq / Hkv);
-        const long long n = (cols * B * Hkv + kSlots - 1) / kSlots;
-        L.pt_cols = (int)(n < 8 ? 8 : n);
-        if ((long long)nblk * B * Hkv >= 4 * 256) L.pt_cols = (int)(most > 1 ? most : 1);
-        L.np_cols = most > 0 ? (int)((most + L.pt_cols - 1) / L.pt_cols) : 1;
-    }
     // token counts padded to a multiple of 64 (the matrix-core path reads whole
     // 64-token tiles and keeps two bf16 arrays where this path keeps one fp32)
     const size_t Tr = (size_t)round_up(T, 64);
@@ -87,8 +60,8 @@ BwdWs bwd_ws_layout(int B, int Hq, int Hkv, int T, int d, int dd, int w, bool mf
     L.ol_off = off;    off += al(rows * dd * 4);
     L.ck_off = off;    off += al(toks * opw);
     L.cv_off = off;    off += al(toks * opw);
-    L.gk_off = off;    off += al(toks * dd * 4 * L.np_cols);
-    L.gv_off = off;    off += al(toks * dd * 4 * L.np_cols);
+    L.gk_off = off;    off += al(toks * dd * 4);
+    L.gv_off = off;    off += al(toks * dd * 4);
     const int G = Hq / Hkv;
     if (mfma) {  // one share per workgroup of 128 keys / 128 query rows
         const int nblk = (T + 127) / 128;

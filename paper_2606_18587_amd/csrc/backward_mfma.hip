@@ -580,17 +580,18 @@ __global__ __launch_bounds__(NW * 64) void bwd_rows_dist_kernel(
 // kernel. Each row's -lse and -delta enter through one more product each,
 // the row-constant operand (hi + mid + lo) against ones3. Writes
 // gK = sum dS q~ (q~ unscaled) and gV = sum P dO~ (fp32) of every real key
-// over the (head, row tile) pairs [pt p, pt p + pt) of part p (bwd_ws_layout)
-// into that part's arrays (a block without distant rows has no part and writes
-// nothing). Grid: np * ceil(T / (32 NW)) * B * Hkv workgroups
+// over the (head, row tile) pairs [pt p, pt p + pt) of part p (col_parts) into
+// that part's arrays, gk, gv for part 0 and array p - 1 of gkx, gvx for the
+// others (a block without distant rows has no part and writes nothing). Grid: np * ceil(T / (32 NW)) * B * Hkv workgroups
 // (xcd_block_head), part 0 first, within a part key block 0 (most rows) first.
 template <int DD, int NW>
 __global__ __launch_bounds__(NW * 64) void bwd_cols_dist_kernel(
     const bf16_t* __restrict__ ckb, const bf16_t* __restrict__ cvb,
     const bf16_t* __restrict__ qts, const bf16_t* __restrict__ qtT,
     const bf16_t* __restrict__ dts, const bf16_t* __restrict__ dtT,
-    const bf16_t* __restrict__ rc, float* __restrict__ gk, float* __restrict__ gv, int Hq,
-    int Hkv, int T, int Tr, int w, float gscale, int BKV, int pt) {
+    const bf16_t* __restrict__ rc, float* __restrict__ gk, float* __restrict__ gv,
+    float* __restrict__ gkx, float* __restrict__ gvx, int Hq, int Hkv, int T, int Tr, int w,
+    float gscale, int BKV, int pt) {
     constexpr int DS = DD / 16, BK = NW * 32;
     static_assert(BK == 128, "bwd_col_tiles");
     constexpr int NQ = 8 * DD, NT = 256, NC = 128;  // 16-byte chunks per 64-row tile
@@ -696,8 +697,9 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_dist_kernel(
         if (live && !interior && t + 63 >= c0 + w && t + 32 < T) step(1, t + 32, true);
     }
     if (!live || j >= T) return;
-    float* gkr = gk + (((size_t)part * BKV + bg) * T + j) * DD;
-    float* gvr = gv + (((size_t)part * BKV + bg) * T + j) * DD;
+    const size_t xrow = (((size_t)imax(part - 1, 0) * BKV + bg) * T + j) * DD;
+    float* gkr = (part == 0 ? gk : gkx) + xrow;
+    float* gvr = (part == 0 ? gv : gvx) + xrow;
 #pragma unroll
     for (int s = 0; s < DS; ++s) {
         const int c = 16 * s + 8 * hg;
@@ -895,9 +897,9 @@ template <int D, int DD, int NW>
 __global__ __launch_bounds__(NW * 64) void bwd_cols_local_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ dout, const bf16_t* __restrict__ wd,
-    const float* __restrict__ gk, const float* __restrict__ gv, const float* __restrict__ nl2,
-    const float* __restrict__ nd, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv,
-    float* __restrict__ wpart, int Hq, int Hkv, int T, int Tr, int w, float qscale, float scale,
+    const float* __restrict__ gk, const float* __restrict__ gv, const float* __restrict__ gkx,
+    const float* __restrict__ gvx, const float* __restrict__ nl2, const float* __restrict__ nd,
+    bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, float* __restrict__ wpart, int Hq, int Hkv, int T, int Tr, int w, float qscale, float scale,
     int nchunk, int BKV, int pt) {
     constexpr int KS = D / 16, NT = D / 32, DS = DD / 16, BN = 64, LDK = D + 8, LDH = 40;
     constexpr int BK = NW * 32;
@@ -1028,8 +1030,9 @@ __global__ __launch_bounds__(NW * 64) void bwd_cols_local_kernel(
             f32x8 kx[DS], vx[DS];
 #pragma unroll
             for (int s = 0; s < DS; ++s) {
-                kx[s] = load_f8(gkr + pt_i * stride + s * 16 + hg * 8);
-                vx[s] = load_f8(gvr + pt_i * stride + s * 16 + hg * 8);
+                const size_t at = (pt_i - 1) * stride + ((size_t)bg * T + jj) * DD + s * 16 + hg * 8;
+                kx[s] = load_f8(gkx + at);
+                vx[s] = load_f8(gvx + at);
             }
 #pragma unroll
             for (int s = 0; s < DS; ++s) {
@@ -1105,6 +1108,37 @@ bool bwd_mfma_supported(int d, int dd, bool bf16) {
     return bf16 && (d == 64 || d == 128) && (dd == 16 || dd == 32);
 }
 
+// Parts of the key-side distant kernel: pt (head, row tile) pairs each, at most
+// np of a key block. With several query heads per KV head its blocks are few
+// and long, and its causal blocks differ in length by the whole sequence: the
+// first one is the time (B2 Hq16 Hkv4 T4001 d128 d_down32 w512: 256 blocks,
+// 267 us). A block's pairs are cut into parts of about one of kSlots equal
+// shares of the whole work, at least 8 tiles each (a part costs about two
+// tiles to start and finish), each with its own fp32 sums, which the window
+// kernel adds in part order: the training step there 717 -> 552 us (with
+// 512 shares: 561). 1 + Hq / Hkv parts fit the workspace. With a block
+// for every resident workgroup already (four on each of 256 compute units)
+// the parts only add their sums (B8 H8 T2048 d64 w256, 1024 blocks: 246.2
+// against 245.3 us), so there is one. The query side has a block per query
+// head and gains nothing from the same cut (83 against 81 us there, 38.3
+// against 36.8 us at B8 H8 T2048 d64 w256).
+struct ColParts {
+    int pt, np;
+};
+static ColParts col_parts(int B, int Hq, int Hkv, int T, int w) {
+    constexpr long long kSlots = 1280;
+    const int nblk = (T + 127) / 128, G = Hq / Hkv;
+    const long long most = (long long)bwd_col_tiles(0, T, w) * G;
+    if (most == 0 || (long long)nblk * B * Hkv >= 4 * 256) return {(int)(most > 1 ? most : 1), 1};
+    long long cols = 0;
+    for (int i = 0; i < nblk; ++i) cols += (long long)bwd_col_tiles(i, T, w) * G;
+    long long pt = (cols * B * Hkv + kSlots - 1) / kSlots;
+    const long long fit = (most + G) / (1 + G);  // so that 1 + G parts are enough
+    pt = pt > fit ? pt : fit;
+    pt = pt > 8 ? pt : 8;
+    return {(int)pt, (int)((most + pt - 1) / pt)};
+}
+
 template <int D, int DD>
 static hipError_t launch_bwd_mfma_t(const bf16_t* q, const bf16_t* k, const bf16_t* v,
                                     const bf16_t* o, const float* lse, const bf16_t* dout,
@@ -1140,23 +1174,46 @@ static hipError_t launch_bwd_mfma_t(const bf16_t* q, const bf16_t* k, const bf16
                        qscale);
     hipLaunchKernelGGL((bwd_prep_keys_kernel<D, DD, NW>), dim3(nprep, B * Hkv), dim3(NW * 64), 0,
                        st, k, v, wd, ckb, ckT, cvb, cvT, Hkv, T, Tr);
-    hipLaunchKernelGGL((bwd_rows_dist_kernel<DD, NW>), dim3(nblk * B * Hq), dim3(NW * 64), 0, st,
-                       (const bf16_t*)ckb, (const bf16_t*)ckT, (const bf16_t*)cvb,
-                       (const bf16_t*)cvT, (const bf16_t*)qts, (const bf16_t*)dts,
-                       (const float*)nl2, (const float*)nd, hk, ol, Hq, Hkv, T, Tr, w, B * Hq);
-    hipLaunchKernelGGL((bwd_cols_dist_kernel<DD, NW>), dim3(L.np_cols * nblk * B * Hkv), dim3(NW * 64),
-                       0, st, (const bf16_t*)ckb, (const bf16_t*)cvb, (const bf16_t*)qts,
-                       (const bf16_t*)qtT, (const bf16_t*)dts, (const bf16_t*)dtT,
-                       (const bf16_t*)rc, gk, gv, Hq, Hkv, T, Tr, w, 1.f / qscale, B * Hkv,
-                       L.pt_cols);
-    hipLaunchKernelGGL((bwd_rows_local_kernel<D, DD, NW>), dim3(nblk * B * Hq), dim3(NW * 64), 0,
-                       st, q, k, v, dout, wd, wu, (const float*)hk, (const float*)ol,
-                       (const float*)nl2, (const float*)nd, dq, part, Hq, Hkv, T, Tr, w,
-                       qscale, scale, L.nchunk, B * Hq);
-    hipLaunchKernelGGL((bwd_cols_local_kernel<D, DD, NW>), dim3(nblk * B * Hkv), dim3(NW * 64), 0,
-                       st, q, k, v, dout, wd, (const float*)gk, (const float*)gv,
-                       (const float*)nl2, (const float*)nd, dk, dv, part, Hq, Hkv, T, Tr, w,
-                       qscale, scale, L.nchunk, B * Hkv, L.pt_cols);
+    const ColParts cp = col_parts(B, Hq, Hkv, T, w);
+    auto cols_dist = [&] {
+        hipLaunchKernelGGL((bwd_cols_dist_kernel<DD, NW>), dim3(cp.np * nblk * B * Hkv), dim3(NW * 64), 0,
+                           st, (const bf16_t*)ckb, (const bf16_t*)cvb, (const bf16_t*)qts,
+                           (const bf16_t*)qtT, (const bf16_t*)dts, (const bf16_t*)dtT,
+                           (const bf16_t*)rc, gk, gv, hk, ol, Hq, Hkv, T, Tr, w, 1.f / qscale, B * Hkv,
+                           cp.pt);
+    };
+    auto cols_local = [&] {
+        hipLaunchKernelGGL((bwd_cols_local_kernel<D, DD, NW>), dim3(nblk * B * Hkv), dim3(NW * 64), 0,
+                           st, q, k, v, dout, wd, (const float*)gk, (const float*)gv, (const float*)hk,
+                           (const float*)ol, (const float*)nl2, (const float*)nd, dk, dv, part, Hq, Hkv,
+                           T, Tr, w, qscale, scale, L.nchunk, B * Hkv, cp.pt);
+    };
+    auto rows_dist = [&] {
+        hipLaunchKernelGGL((bwd_rows_dist_kernel<DD, NW>), dim3(nblk * B * Hq), dim3(NW * 64), 0, st,
+                           (const bf16_t*)ckb, (const bf16_t*)ckT, (const bf16_t*)cvb,
+                           (const bf16_t*)cvT, (const bf16_t*)qts, (const bf16_t*)dts,
+                           (const float*)nl2, (const float*)nd, hk, ol, Hq, Hkv, T, Tr, w, B * Hq);
+    };
+    auto rows_local = [&] {
+        hipLaunchKernelGGL((bwd_rows_local_kernel<D, DD, NW>), dim3(nblk * B * Hq), dim3(NW * 64), 0,
+                           st, q, k, v, dout, wd, wu, (const float*)hk, (const float*)ol,
+                           (const float*)nl2, (const float*)nd, dq, part, Hq, Hkv, T, Tr, w,
+                           qscale, scale, L.nchunk, B * Hq);
+    };
+    if (cp.np > 1) {
+        // the key side first: until the row side runs, hk and ol hold its parts
+        cols_dist();
+        cols_local();
+        rows_dist();
+        rows_local();
+    } else {
+        // (both distant kernels read the latents, both window kernels q and
+        // dO: in the order above B8 H8 T2048 d64 w256 takes 0.9 % longer)
+        rows_dist();
+        cols_dist();
+        rows_local();
+        cols_local();
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_bwd_wreduce(part, dwd, dwu, Hkv, D, DD, L, st);

@@ -269,8 +269,13 @@ RopeBwdWs rope_bwd_ws_layout(const dar_shape* s, int T) {
     put(L.vd, B * Hkv * Td * d * 2);
     put(L.nl2, B * Hq * Tr * 4);
     put(L.nd, B * Hq * Tr * 4);
-    L.nchunk = (int)B * ((T + 127) / 128);  // one share per workgroup of 128 keys
-    put(L.wpart, 2 * Hkv * (size_t)L.nchunk * d * dd * 4);
+    // one share per workgroup of 128 keys; the size asked of the caller stays
+    // that of the fp32 gradient arrays (rows, window and distant keys) and a
+    // share per 32 keys, which contains it: programs hold buffers of that size
+    L.nchunk = (int)B * ((T + 127) / 128);
+    L.wpart = off;
+    off += al(B * Hq * T * d * 4) + 2 * al(B * Hkv * T * d * 4) + 2 * al(B * Hkv * Td * d * 4);
+    off += al(2 * Hkv * B * ((T + 31) / 32) * d * dd * 4);
     L.bytes = off;
     return L;
 }
@@ -415,8 +420,8 @@ dar_status dar_attn_prefill_rope(const dar_shape* s, int T, int pos0, const dar_
 size_t dar_prefill_backward_workspace_bytes(const dar_shape* s, int T) {
     if (check_shape(s) != DAR_OK || T < 1) return 0;
     // enough for either kernel family (DAR_BWD_VALU may pick the generic one)
-    const size_t a = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, s->w, false).bytes;
-    const size_t b = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, s->w, true).bytes;
+    const size_t a = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, false).bytes;
+    const size_t b = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, true).bytes;
     return a > b ? a : b;
 }
 
@@ -504,7 +509,7 @@ dar_status dar_attn_prefill_backward(const dar_shape* s, int T, const void* q, c
     hipError_t e;
     const bool fast = bwd_mfma_supported(s->d, s->d_down, s->dtype == DAR_BF16) &&
                       !env_flag("DAR_BWD_VALU");
-    const BwdWs L = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, s->w, fast);
+    const BwdWs L = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, fast);
     if (fast)
         e = launch_bwd_mfma((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)o,
                             lse, (const bf16_t*)dout, (const bf16_t*)w_down, (const bf16_t*)w_up,

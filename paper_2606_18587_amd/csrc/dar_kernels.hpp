@@ -200,17 +200,15 @@ hipError_t launch_append_shared(const T* k_new, const T* v_new, const T* c_new, 
 //                                         hi + mid + lo bf16 triple (row constants)
 //   hk, ol            [B*Hq][T][dd] fp32  sum dS c^K, sum P c^V per row
 //   ck, cv            [B*Hkv][Tr]         latents, laid out as qt
-//   gk, gv            [np_cols][B*Hkv][T][dd] fp32 sum dS q~, sum P dO~ per key
-//                                         (one array per part of the row tiles)
+//   gk, gv            [B*Hkv][T][dd] fp32 sum dS q~, sum P dO~ per key (the
+//                                         matrix-core path's parts past the first
+//                                         lie in hk and ol, which are written later)
 //   wpart             [2][Hkv][nchunk][d][dd]  weight-gradient partials per chunk
 // (each array region is sized for Tr tokens).
 struct BwdWs {
     size_t lse_off, delta_off, qt_off, dot_off, rc_off, hk_off, ol_off, ck_off, cv_off, gk_off,
         gv_off, wpart_off, bytes;
     int nchunk_d, nchunk_u, nchunk;
-    // matrix-core path: 64-row tiles of one part, and the most parts of a
-    // 128-key block (1 elsewhere)
-    int pt_cols, np_cols;
 };
 
 // 64-row tiles (of one query head) with a distant pair for 128-key block blk.
@@ -218,16 +216,14 @@ __host__ __device__ inline int bwd_col_tiles(int blk, int T, int w) {
     const long long t0 = ((long long)128 * blk + w) & ~63LL;
     return t0 < T ? (int)((T - 1 - t0) / 64) + 1 : 0;
 }
-// Row chunks of the weight-gradient reduction: about 16 rows each, at most 128
-// (with 256 rows each, B1 H8 T331 d64 had 32 workgroups of one row at a time:
-// 183 of the training step's 605 us).
+// Row chunks of the weight-gradient reduction: about 256 rows each, at most 128.
 static inline int bwd_nchunk(long long rows) {
-    long long n = (rows + 15) / 16;
+    long long n = (rows + 255) / 256;
     return (int)(n < 1 ? 1 : (n > 128 ? 128 : n));
 }
 // mfma: chunks of the weight-gradient shares are the matrix-core kernels'
 // workgroups (else row chunks of the vector-ALU reduction).
-BwdWs bwd_ws_layout(int B, int Hq, int Hkv, int T, int d, int dd, int w, bool mfma);
+BwdWs bwd_ws_layout(int B, int Hq, int Hkv, int T, int d, int dd, bool mfma);
 hipError_t launch_bwd_wreduce(const float* part, float* dwd, float* dwu, int Hkv, int d, int dd,
                               const BwdWs& L, hipStream_t st);
 

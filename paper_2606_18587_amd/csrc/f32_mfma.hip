@@ -21,7 +21,7 @@
 // products and exponentials is the time; 16-row wavefronts keep that chain
 // short and give T / 16 wavefronts a head. Forward and backward at B1 H8 T331
 // d64 d_down16 w64 took 605 us with one wavefront per row on the vector ALUs
-// (every lane reading its own key row element by element), 124 us here.
+// (every lane reading its own key row element by element), 130 us here.
 //
 // A masked pair (after the row, outside the region) has weight exactly zero,
 // but a product multiplies it all the same: a subtile with masked pairs whose
@@ -617,27 +617,34 @@ __global__ __launch_bounds__(64) void bwd_f32_cols_kernel(
 // Weight-gradient share of one chunk of rows, stored [e][c], as
 // bwd_wpart_kernel: z = 0 sum k_e (s gK_c) + v_e gV_c over the tokens of KV
 // head g, z = 1 sum q_e (s h_c) + dO_e ol_c over its group's query rows; the
-// rows are the products' k, four at a step. One wavefront per (chunk, KV head,
-// z, 16 columns); grid (nchunk, Hkv, 2 * DD / 16).
+// rows are the products' k, four at a step. One workgroup per (chunk, KV head,
+// z, 16 columns), its eight wavefronts an eighth of the rows each (a chunk is
+// 256 rows or more: with one wavefront a chunk, 64 dependent steps), added in
+// order in LDS. Grid (nchunk, Hkv, 2 * DD / 16).
+constexpr int kPartWaves = 8;
 template <int D, int DD>
-__global__ __launch_bounds__(64) void bwd_f32_wpart_kernel(
+__global__ __launch_bounds__(64 * kPartWaves) void bwd_f32_wpart_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ dout, const float* __restrict__ gk, const float* __restrict__ gv,
     const float* __restrict__ hk, const float* __restrict__ ol, float* __restrict__ part, int B,
     int Hq, int Hkv, int T, int d, int dd, int nchunk_d, int nchunk_u, int nchunk, float scale) {
     constexpr int NT = D / 16;
-    const int lane = lane_id_x(), qd = lane >> 4, c16 = lane & 15;
+    __shared__ f32x4_t sum[NT][64];
+    const int tid = lane_id_x(), lane = tid & 63, qd = lane >> 4, c16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int chunk = wg_id_x(), g = wg_id_y();
     const int z = wg_id_z() & 1, ct = wg_id_z() >> 1;
     const int nch = z == 0 ? nchunk_d : nchunk_u;
-    if (chunk >= nch || 16 * ct >= dd) return;
+    if (chunk >= nch || 16 * ct >= dd) return;  // workgroup-uniform
     const int H = z == 0 ? Hkv : Hq, n = z == 0 ? 1 : Hq / Hkv;  // heads of an array, of the group
     const float *x1 = z == 0 ? k : q, *x2 = z == 0 ? v : dout;
     const float *y1 = z == 0 ? gk : hk, *y2 = z == 0 ? gv : ol;
     const long long rows = (long long)B * n * T;
     const long long per = (rows + nch - 1) / nch;
-    const long long r0 = (long long)chunk * per;
-    const long long r1 = r0 + per < rows ? r0 + per : rows;
+    const long long end = (chunk + 1) * per < rows ? (chunk + 1) * per : rows;
+    const long long wper = (per + 4 * kPartWaves - 1) / (4 * kPartWaves) * 4;
+    const long long r0 = (long long)chunk * per + wave * wper;
+    const long long r1 = r0 + wper < end ? r0 + wper : end;
     const int c = 16 * ct + c16;
     f32x4_t acc[NT];
 #pragma unroll
@@ -663,14 +670,21 @@ __global__ __launch_bounds__(64) void bwd_f32_wpart_kernel(
             acc[t] = mma(e < d_r ? a2 : 0.f, c < dd_r ? b2 : 0.f, acc[t]);
         }
     }
+    for (int wv = 0; wv < kPartWaves; ++wv) {
+        if (wave == wv) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) sum[t][lane] = wv == 0 ? acc[t] : sum[t][lane] + acc[t];
+        }
+        __syncthreads();
+    }
     float* out = part + (((size_t)z * Hkv + g) * nchunk + chunk) * (size_t)d * dd;
-    if (c >= dd) return;
+    if (wave != 0 || c >= dd) return;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int e = 16 * t + 4 * qd + r;
-            if (e < d) out[(size_t)e * dd + c] = acc[t][r];
+            if (e < d) out[(size_t)e * dd + c] = sum[t][lane][r];
         }
 }
 
@@ -737,7 +751,7 @@ hipError_t launch_bwd_f32(const float* q, const float* k, const float* v, const 
                        (const float*)dot, (const float*)delta, lse, gk, gv, dk, dv, Hq, Hkv, T, d,  \
                        dd, w, scale);                                                               \
     hipLaunchKernelGGL((bwd_f32_wpart_kernel<D_, DD_>), dim3(L.nchunk, Hkv, 2 * (DD_ / 16)),        \
-                       dim3(64), 0, st, q, k, v, dout, (const float*)gk, (const float*)gv,          \
+                       dim3(64 * kPartWaves), 0, st, q, k, v, dout, (const float*)gk, (const float*)gv,          \
                        (const float*)hk, (const float*)ol, part, B, Hq, Hkv, T, d, dd, L.nchunk_d,  \
                        L.nchunk_u, L.nchunk, scale)
     DAR_F32_DISPATCH(DAR_F32_CALL);
