@@ -61,13 +61,13 @@ CSRC = os.path.join(ROOT, "paper_2606_18587_amd", "csrc")
 MEASURED_TRAFFIC = {
     "prefill": {"files": ["dar_api.hip", "dar_common.hpp", "dar_kernels.hpp", "latent.hip",
                           "prefill_mfma.hip"],
-                "sha256_16": "78f2401ce7252071", "bytes": 126117468},
+                "sha256_16": "3f4b701fa890b594", "bytes": 126122004},
     "decode": {"files": ["dar_api.hip", "dar_common.hpp", "dar_kernels.hpp", "decode.hip",
                          "decode_mfma.hip"],
-               "sha256_16": "6556aad07ed64880", "bytes": 563628767},
+               "sha256_16": "487397547ecf0358", "bytes": 563903519},
     "backward": {"files": ["dar_api.hip", "dar_common.hpp", "dar_kernels.hpp", "mfma_common.hpp",
                            "backward.hip", "backward_mfma.hip"],
-                 "sha256_16": "a2ed4e6dfcfdec0a", "bytes": 502792476},
+                 "sha256_16": "15349d2b038086b3", "bytes": 502168977},
 }
 
 

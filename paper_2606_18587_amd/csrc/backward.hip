@@ -1,6 +1,6 @@
-// Backward of the causal DAR prefill on the vector ALUs (every shape and
-// dtype), plus the preparation and weight-gradient kernels that the
-// matrix-core backward shares.
+// Backward of the causal DAR prefill on the vector ALUs (takes every
+// shape and dtype; runs those the matrix-core kernels do not cover), plus the
+// preparation and weight-gradient kernels that the matrix-core backward shares.
 //
 // For L = sum(dO * O) (the training objective's attention part, Section 2.3)
 // with S_ij = q_i . key_ij / sqrt(d), P = softmax(S) row by row and

@@ -1,5 +1,5 @@
-// Generic causal DAR prefill on the vector ALUs (fp32 path, and the fallback
-// for bf16 head sizes the matrix-core kernel does not cover).
+// Generic causal DAR prefill on the vector ALUs (the fp32 and bf16 head sizes
+// that the matrix-core kernels do not cover).
 //
 // One wavefront per (query row, batch * query head); row r is the query at
 // position i = q0 + r (q0 = 0 for a whole sequence, the cache length for a
