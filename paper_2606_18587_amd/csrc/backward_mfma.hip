@@ -1295,7 +1295,8 @@ __global__ __launch_bounds__(256) void bwd_rope_rowprep_kernel(const bf16_t* __r
 
 // Dynamic LDS: the rows kernel's two tiles, or its wavefronts' fp32 rows; the
 // keys kernel's part below the weights (a wavefront's fp32 rows, or its bf16
-// tile with two latent tiles; the tiles and row constants fit in the same).
+// tile with a latent tile's two parts; the tiles and row constants fit in the
+// same).
 __host__ __device__ constexpr int rope_rows_lds_bytes(int D, int NW) {
     return 2 * 64 * (D + 8) * 2 > NW * 32 * (D + 4) * 4 ? 2 * 64 * (D + 8) * 2 : NW * 32 * (D + 4) * 4;
 }
@@ -1524,7 +1525,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
     extern __shared__ __align__(16) char sm[];
     // Q tile, dO tile, -lse and -delta of their rows; between and after the
     // regions the wavefronts' scratch (fp32 rows for the rotation, or a bf16
-    // tile and two latent tiles) and the weight shares' sum
+    // tile and a latent tile's two parts) and the weight shares' sum
     bf16_t* lds_q = reinterpret_cast<bf16_t*>(sm);
     bf16_t* lds_do = lds_q + BN * LDK;
     float* lds_lse = reinterpret_cast<float*>(lds_do + BN * LDK);
@@ -1648,8 +1649,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
 
     float* F = reinterpret_cast<float*>(sm + wave * (rope_keys_scratch_bytes(D, NW) / NW));
     bf16_t* xs = reinterpret_cast<bf16_t*>(F);  // [32][LDK]: 32 tokens at full d
-    bf16_t* yh = xs + 32 * LDK;                 // [32][LDH]: a 32-column latent tile, hi
-    bf16_t* yl = yh + 32 * LDH;                 // ... lo
+    bf16_t* ys = xs + 32 * LDK;                 // [2][32][LDH]: a 32-column latent tile, hi, lo
     const float* tabp = tab + (size_t)(pos0 + jj) * r;
     const bool any_dist = live && c0 + w < T;  // wave-uniform
     const int nkb = (T + BK - 1) / BK;
@@ -1659,45 +1659,91 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
     if (Td > cwg_lo) region(kd, vd, Td, true);  // (workgroup-uniform) some key is distant for some row
     else __syncthreads();                       // the weights are staged
     rotate_tile<D, false>(dkT, scale, F, r, tabp, qc, hg);  // u
-    bf16x8_t uh[KS], ul[KS], dh[KS], dl[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        split8(dkT[s >> 1], 8 * (s & 1), 1.f, uh[s], ul[s]);
-        split8(dvT[s >> 1], 8 * (s & 1), 1.f, dh[s], dl[s]);
-    }
+    // u and dvd stay in fp32 and are split where they enter a product
+    f32x16_t u[NT], dvd[NT];
     // gK W_down^T and gV W_down^T; the window's sums are added on top, the
     // first (rotated forward, over s) in the rotated keys' frame
 #pragma unroll
-    for (int t = 0; t < NT; ++t) { dkT[t] = splat16(0.f); dvT[t] = splat16(0.f); }
-    const bf16_t* kp = k + ((size_t)bg * T + jj) * D + hg * 8;
-    const bf16_t* vp = v + ((size_t)bg * T + jj) * D + hg * 8;
-    // acc[e][c] += sum_j X[j][e] (Yh + Yl)[j][c], Y: columns c of token qc
-    auto put_y = [&](const bf16x8_t (&hi)[2], const bf16x8_t (&lo)[2]) {
-#pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2) {
-            *reinterpret_cast<bf16x8_t*>(yh + qc * LDH + 16 * h2 + 8 * hg) = hi[h2];
-            *reinterpret_cast<bf16x8_t*>(yl + qc * LDH + 16 * h2 + 8 * hg) = lo[h2];
-        }
-    };
-    auto share = [&](f32x16_t (&acc)[NT], const bf16x8_t (&x)[KS], bool with_lo) {
+    for (int t = 0; t < NT; ++t) {
+        u[t] = dkT[t];
+        dvd[t] = dvT[t];
+        dkT[t] = splat16(0.f);
+        dvT[t] = splat16(0.f);
+    }
+    const size_t own = ((size_t)bg * T + jj) * D + hg * 8;
+    // acc[e][c] += sum_j X[j][e] Y[j][c] with the parts hi .. of Y down to part
+    // `last` (smallest first); x(s): step s of this lane's token
+    auto share = [&](f32x16_t (&acc)[NT], auto x, int last) {
 #pragma unroll
         for (int s = 0; s < KS; ++s)
-            *reinterpret_cast<bf16x8_t*>(xs + qc * LDK + s * 16 + hg * 8) = x[s];
+            *reinterpret_cast<bf16x8_t*>(xs + qc * LDK + s * 16 + hg * 8) = x(s);
         wave_lds_order();
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
-            const bf16x8_t bh = lds_tr_operand(yh, LDH, hf * 16, 0, lane);
-            const bf16x8_t bl = lds_tr_operand(yl, LDH, hf * 16, 0, lane);
+            bf16x8_t y[2];
+#pragma unroll
+            for (int p = 0; p <= last; ++p) y[p] = lds_tr_operand(ys + p * 32 * LDH, LDH, hf * 16, 0, lane);
 #pragma unroll
             for (int tt = 0; tt < NT; ++tt) {
                 const bf16x8_t a = lds_tr_operand(xs, LDK, hf * 16, tt * 32, lane);
-                if (with_lo) acc[tt] = mfma(a, bl, acc[tt]);
-                acc[tt] = mfma(a, bh, acc[tt]);
+#pragma unroll
+                for (int p = last; p >= 0; --p) acc[tt] = mfma(a, y[p], acc[tt]);
             }
         }
         wave_lds_order();
     };
+    // one of the two sides (keys: u, k, dkT; values: dvd, v, dvT) of 32 columns,
+    // so that no instance spills a register: with the sides and the column tiles
+    // side by side d = 128, d_down > 32 took all 512 and scratch besides, and a
+    // tuple spilled partly to accumulation registers and partly to scratch may
+    // come back incomplete (tests/test_kernel_resources.py).
+    // up 0: gX = x W_up^T, dW_down += row^T gX, g += gX W_down^T;
+    // up 1: cX = row W_down, dW_up^T += x^T cX
+    auto side = [&](int up, int ct, const f32x16_t (&x)[NT], const bf16_t* rows, f32x16_t (&g)[NT],
+                    f32x16_t (&pw)[NT]) {
+        f32x16_t y = splat16(0.f);
 #pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const bf16x8_t a = load_bf16x8((up ? wds : wus) + (32 * ct + prow) * LDK + s * 16 + hg * 8);
+            if (up) {
+                y = mfma(a, load_bf16x8(rows + own + s * 16), y);
+            } else {
+                bf16x8_t xp[2];
+                split8(x[s >> 1], 8 * (s & 1), 1.f, xp[0], xp[1]);
+#pragma unroll
+                for (int p = 1; p >= 0; --p) y = mfma(a, xp[p], y);
+            }
+        }
+#pragma unroll
+        for (int h2 = 0; h2 < 2; ++h2) {
+            bf16x8_t yp[2];
+            split8(y, 8 * h2, 1.f, yp[0], yp[1]);
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+                *reinterpret_cast<bf16x8_t*>(ys + (p * 32 + qc) * LDH + 16 * h2 + 8 * hg) = yp[p];
+            if (up == 0) {
+#pragma unroll
+                for (int tt = 0; tt < NT; ++tt) {
+                    const bf16x8_t a = lds_tr_operand_perm(wds, LDK, 32 * ct + 16 * h2, 32 * tt, lane);
+#pragma unroll
+                    for (int p = 1; p >= 0; --p) g[tt] = mfma(a, yp[p], g[tt]);
+                }
+            }
+        }
+        if (up) {
+            // lo hi, then hi (lo, hi)
+#pragma unroll
+            for (int p = 1; p >= 0; --p)
+                share(pw, [&](int s) {
+                    bf16x8_t xp[2];
+                    split8(x[s >> 1], 8 * (s & 1), 1.f, xp[0], xp[1]);
+                    return xp[p];
+                }, 1 - p);
+        } else {
+            share(pw, [&](int s) { return load_bf16x8(rows + own + s * 16); }, 1);
+        }
+    };
+#pragma nounroll
     for (int ct = 0; ct < DT; ++ct)
 #pragma unroll
         for (int up = 0; up < 2; ++up) {
@@ -1705,50 +1751,9 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
 #pragma unroll
             for (int t = 0; t < NT; ++t) pw[t] = splat16(0.f);
             if (any_dist) {
-                // up 0: gK, gV; 1: cK, cV (32 columns of this lane's token)
-                f32x16_t yk = splat16(0.f), yv = splat16(0.f);
-                bf16x8_t kB[KS], vB[KS], kh[2], kl[2], vh[2], vl[2];
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    kB[s] = load_bf16x8(kp + s * 16);
-                    vB[s] = load_bf16x8(vp + s * 16);
-                }
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    const bf16x8_t a =
-                        load_bf16x8((up ? wds : wus) + (32 * ct + prow) * LDK + s * 16 + hg * 8);
-                    if (up == 0) {
-                        yk = mfma(a, ul[s], yk);
-                        yv = mfma(a, dl[s], yv);
-                    }
-                    yk = mfma(a, up ? kB[s] : uh[s], yk);
-                    yv = mfma(a, up ? vB[s] : dh[s], yv);
-                }
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2) {
-                    split8(yk, 8 * h2, 1.f, kh[h2], kl[h2]);
-                    split8(yv, 8 * h2, 1.f, vh[h2], vl[h2]);
-                }
                 wave_lds_order();
-                put_y(kh, kl);
-                if (up) share(pw, ul, false);
-                share(pw, up ? uh : kB, true);
-                put_y(vh, vl);
-                if (up) share(pw, dl, false);
-                share(pw, up ? dh : vB, true);
-                if (up == 0) {
-#pragma unroll
-                    for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-                        for (int tt = 0; tt < NT; ++tt) {
-                            const bf16x8_t a =
-                                lds_tr_operand_perm(wds, LDK, 32 * ct + 16 * h2, 32 * tt, lane);
-                            dkT[tt] = mfma(a, kl[h2], dkT[tt]);
-                            dvT[tt] = mfma(a, vl[h2], dvT[tt]);
-                            dkT[tt] = mfma(a, kh[h2], dkT[tt]);
-                            dvT[tt] = mfma(a, vh[h2], dvT[tt]);
-                        }
-                }
+                side(up, ct, u, k, dkT, pw);
+                side(up, ct, dvd, v, dvT, pw);
             }
             // the wavefronts' shares added in order (pbuf is the scratch)
             __syncthreads();

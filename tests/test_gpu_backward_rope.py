@@ -108,6 +108,23 @@ def test_chain_rule_column_tiles(d, dd, w, T, r):
     full_compare(wl, r, pos0=3)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,d,dd,w,r",
+                         [(2, 2, 2, 300, 128, 64, 150, 32), (2, 8, 1, 290, 128, 64, 40, 128),
+                          (2, 4, 4, 400, 128, 73, 200, 16), (2, 8, 1, 270, 128, 65, 129, 34),
+                          (1, 8, 1, 300, 64, 64, 140, 64), (2, 4, 4, 390, 64, 33, 5, 16)])
+def test_wide_latents_over_several_key_blocks(B, Hq, Hkv, T, d, dd, w, r):
+    """Two and three column tiles up to the largest accepted d_down, with
+    distant rows for several blocks of 128 keys, windows longer than one, one
+    or eight query heads a KV head (untied and tied). ELEM_BOUND holds for the
+    weight gradients while their largest entry stays below about 60: their
+    error, the rounding of the summands, is about 0.2 of the normwise bound
+    whatever the entry, so a small entry's is 0.2 max |dW| of its own (one
+    sequence where eight heads and a short head size would pass that)."""
+    wl = di.Workload("rope_bwd_wide", 54, B, Hq, Hkv, T, d, dd, w, "bf16")
+    full_compare(wl, r, untied=True)
+    full_compare(wl, r, pos0=1)
+
+
 def test_offset_positions_and_zero_rotary_dim():
     """Rows at positions 77.. of a longer sequence, and r = 0, whose gradients
     are those of the plain backward (checked against the oracle's)."""
