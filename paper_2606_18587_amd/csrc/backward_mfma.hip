@@ -1295,14 +1295,14 @@ __global__ __launch_bounds__(256) void bwd_rope_rowprep_kernel(const bf16_t* __r
 
 // Dynamic LDS: the rows kernel's two tiles, or its wavefronts' fp32 rows; the
 // keys kernel's part below the weights (a wavefront's fp32 rows, or its bf16
-// tile with a latent tile's two parts; the tiles and row constants fit in the
+// tile with a latent tile's three parts; the tiles and row constants fit in the
 // same).
 __host__ __device__ constexpr int rope_rows_lds_bytes(int D, int NW) {
     return 2 * 64 * (D + 8) * 2 > NW * 32 * (D + 4) * 4 ? 2 * 64 * (D + 8) * 2 : NW * 32 * (D + 4) * 4;
 }
 __host__ __device__ constexpr int rope_keys_scratch_bytes(int D, int NW) {
-    return NW * (32 * (D + 4) * 4 > 32 * (D + 8) * 2 + 2 * 32 * 40 * 2 ? 32 * (D + 4) * 4
-                                                                       : 32 * (D + 8) * 2 + 2 * 32 * 40 * 2);
+    return NW * (32 * (D + 4) * 4 > 32 * (D + 8) * 2 + 3 * 32 * 40 * 2 ? 32 * (D + 4) * 4
+                                                                       : 32 * (D + 8) * 2 + 3 * 32 * 40 * 2);
 }
 static_assert(rope_keys_scratch_bytes(64, 4) >= 2 * 64 * 72 * 2 + 2 * 64 * 4 &&
                   rope_keys_scratch_bytes(128, 4) >= 2 * 64 * 136 * 2 + 2 * 64 * 4 &&
@@ -1503,14 +1503,16 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_rows_kernel(
 //   dW_down += k^T gK + v^T gV,  dW_up^T += u^T cK + dvd^T cV  (shares)
 //   dk = R^T s dkr + gK W_down^T,  dv = dvw + gV W_down^T
 // on the matrix cores; u, dvd, gK, gV, cK, cV are fp32 sums and enter as bf16
-// hi + lo pairs (two fp32 factors as hi hi + hi lo + lo hi: about 16
-// significant bits, against the 8 of the P and dS they were summed from). The
-// chain rule adds about 75 products per wavefront to the 16 of each of its
-// 32-row subtiles (on the vector ALUs it took 190 us at B4 H16 T2048 d64
-// d_down16 w128; forward and backward together went from 550 to 346 us).
-// The window's sums start from gK W_down^T and gV W_down^T instead of keeping
-// gK and gV in registers through the window's loop. d_down <= 32 DT columns, zero padded. Writes the share of
-// chunk b * nkb + key block. Grid: ceil(T / (32 NW)) * B * Hkv workgroups
+// triples hi + mid + lo, so that a product with a bf16 factor carries the 24
+// bits of fp32 (three products) and one of two fp32 factors as well (six). The
+// chain rule adds about 130 products per wavefront to the 16 of each of its
+// 32-row subtiles at d = 64: forward and backward at B4 H16 T2048 d64 d_down16
+// w128 take 348 us (550 with the chain rule on the vector ALUs; 338 with hi +
+// lo pairs, 75 products, whose weight gradients carried 16 bits: 2^-16.5 of the
+// summed magnitudes off where the triples are 2^-22). The window's sums start from gK W_down^T and gV W_down^T
+// instead of keeping gK and gV in registers through the window's loop. d_down
+// <= 32 DT columns, zero padded. Writes the share of chunk b * nkb + key block.
+// Grid: ceil(T / (32 NW)) * B * Hkv workgroups
 // (xcd_block_head), key block 0 (most rows) first.
 template <int D, int DT, int NW>
 __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
@@ -1525,7 +1527,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
     extern __shared__ __align__(16) char sm[];
     // Q tile, dO tile, -lse and -delta of their rows; between and after the
     // regions the wavefronts' scratch (fp32 rows for the rotation, or a bf16
-    // tile and a latent tile's two parts) and the weight shares' sum
+    // tile and a latent tile's three parts) and the weight shares' sum
     bf16_t* lds_q = reinterpret_cast<bf16_t*>(sm);
     bf16_t* lds_do = lds_q + BN * LDK;
     float* lds_lse = reinterpret_cast<float*>(lds_do + BN * LDK);
@@ -1649,7 +1651,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
 
     float* F = reinterpret_cast<float*>(sm + wave * (rope_keys_scratch_bytes(D, NW) / NW));
     bf16_t* xs = reinterpret_cast<bf16_t*>(F);  // [32][LDK]: 32 tokens at full d
-    bf16_t* ys = xs + 32 * LDK;                 // [2][32][LDH]: a 32-column latent tile, hi, lo
+    bf16_t* ys = xs + 32 * LDK;                 // [3][32][LDH]: a 32-column latent tile, hi, mid, lo
     const float* tabp = tab + (size_t)(pos0 + jj) * r;
     const bool any_dist = live && c0 + w < T;  // wave-uniform
     const int nkb = (T + BK - 1) / BK;
@@ -1680,7 +1682,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
         wave_lds_order();
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
-            bf16x8_t y[2];
+            bf16x8_t y[3];
 #pragma unroll
             for (int p = 0; p <= last; ++p) y[p] = lds_tr_operand(ys + p * 32 * LDH, LDH, hf * 16, 0, lane);
 #pragma unroll
@@ -1708,39 +1710,40 @@ __global__ __launch_bounds__(NW * 64) void bwd_rope_keys_kernel(
             if (up) {
                 y = mfma(a, load_bf16x8(rows + own + s * 16), y);
             } else {
-                bf16x8_t xp[2];
-                split8(x[s >> 1], 8 * (s & 1), 1.f, xp[0], xp[1]);
+                bf16x8_t xp[3];
+                split8x3(x[s >> 1], 8 * (s & 1), xp);
 #pragma unroll
-                for (int p = 1; p >= 0; --p) y = mfma(a, xp[p], y);
+                for (int p = 2; p >= 0; --p) y = mfma(a, xp[p], y);
             }
         }
 #pragma unroll
         for (int h2 = 0; h2 < 2; ++h2) {
-            bf16x8_t yp[2];
-            split8(y, 8 * h2, 1.f, yp[0], yp[1]);
+            bf16x8_t yp[3];
+            split8x3(y, 8 * h2, yp);
 #pragma unroll
-            for (int p = 0; p < 2; ++p)
+            for (int p = 0; p < 3; ++p)
                 *reinterpret_cast<bf16x8_t*>(ys + (p * 32 + qc) * LDH + 16 * h2 + 8 * hg) = yp[p];
             if (up == 0) {
 #pragma unroll
                 for (int tt = 0; tt < NT; ++tt) {
                     const bf16x8_t a = lds_tr_operand_perm(wds, LDK, 32 * ct + 16 * h2, 32 * tt, lane);
 #pragma unroll
-                    for (int p = 1; p >= 0; --p) g[tt] = mfma(a, yp[p], g[tt]);
+                    for (int p = 2; p >= 0; --p) g[tt] = mfma(a, yp[p], g[tt]);
                 }
             }
         }
         if (up) {
-            // lo hi, then hi (lo, hi)
+            // every product of the two factors' parts that reaches 2^-24: lo hi,
+            // mid (mid, hi), hi (lo, mid, hi)
 #pragma unroll
-            for (int p = 1; p >= 0; --p)
+            for (int p = 2; p >= 0; --p)
                 share(pw, [&](int s) {
-                    bf16x8_t xp[2];
-                    split8(x[s >> 1], 8 * (s & 1), 1.f, xp[0], xp[1]);
+                    bf16x8_t xp[3];
+                    split8x3(x[s >> 1], 8 * (s & 1), xp);
                     return xp[p];
-                }, 1 - p);
+                }, 2 - p);
         } else {
-            share(pw, [&](int s) { return load_bf16x8(rows + own + s * 16); }, 1);
+            share(pw, [&](int s) { return load_bf16x8(rows + own + s * 16); }, 2);
         }
     };
 #pragma nounroll

@@ -60,6 +60,25 @@ __device__ __forceinline__ void split8(const f32x16_t& x, int o, float f, bf16x8
     lo = __builtin_bit_cast(bf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
 }
 
+// x[o..o+7] as a bf16 triple hi + mid + lo (each the rounded rest of the ones
+// before): three products carry the 24 significant bits of fp32.
+__device__ __forceinline__ void split8x3(const f32x16_t& x, int o, bf16x8_t (&part)[3]) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = x[o + k];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        uint32_t h[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            h[k] = pack2(v[2 * k], v[2 * k + 1]);
+            v[2 * k] -= __uint_as_float(h[k] << 16);
+            v[2 * k + 1] -= __uint_as_float(h[k] & 0xffff0000u);
+        }
+        part[p] = __builtin_bit_cast(bf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
+    }
+}
+
 __device__ __forceinline__ f32x16_t mfma(bf16x8_t a, bf16x8_t b, f32x16_t c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }

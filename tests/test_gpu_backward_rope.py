@@ -125,6 +125,97 @@ def test_wide_latents_over_several_key_blocks(B, Hq, Hkv, T, d, dd, w, r):
     full_compare(wl, r, pos0=1)
 
 
+def exact_chain_inputs(rng, B, Hq, Hkv, T, d, dd, w):
+    """Inputs whose distant scores are zero and whose P, dS and sums before the
+    chain rule are exact, so that only the chain rule can round:
+      * d splits into L = 16..d/2-1 (queries) and U = d/2..d-1 (lifted keys), and
+        the latent columns into A (the keys' and values') and the rest C; W_up
+        sends A into U and C into L, W_down fills A alone, keys lie in U: the
+        scores are 0 and, with lse = 0, P = 1;
+      * values are one element each that W_down and W_up send to the one element z
+        of U, and o = 0: dS = dO[z] 2^m, a bf16 number;
+      * entries are whole numbers: u / s and dvd are whole numbers below 2^24.
+    w = T - 10: ten distant keys. Returns torch-free fp64 arrays."""
+    h = d // 2
+    nA = dd // 2
+    perm = rng.permutation(h)
+    z, ups = h + perm[0], h + perm[1:]
+    ys, xs = ups[:5], ups[5:15]  # rows of W_down that the values and the keys use
+    wd = np.zeros((Hkv, d, dd))
+    wu = np.zeros((Hkv, dd, d))
+    for g in range(Hkv):
+        wd[g, ys, 0] = 1.0
+        for n, x in enumerate(xs):
+            wd[g, x, 1 + n % (nA - 1)] = rng.integers(129, 256)
+        wu[g, 0, z] = 1.0
+        for c in range(1, nA):
+            wu[g, c, ups[rng.integers(len(ups))]] = rng.integers(1, 9)
+        for c in range(nA, dd):
+            wu[g, c, rng.integers(16, h)] = rng.integers(129, 256)
+    q = np.zeros((B, Hq, T, d))
+    q[..., 16:h] = rng.integers(-255, 256, (B, Hq, T, h - 16))
+    dout = rng.integers(-255, 256, (B, Hq, T, d)) * 2.0 ** rng.integers(0, 5, (B, Hq, T, d))
+    dout[..., z] = rng.integers(-3, 4, (B, Hq, T)) * 2.0 ** rng.integers(0, 6, (B, Hq, T))
+    k = np.zeros((B, Hkv, T, d))
+    v = np.zeros((B, Hkv, T, d))
+    for t in range(T):
+        k[:, :, t, xs[t % 10]] = rng.integers(129, 256, (B, Hkv))
+        v[:, :, t, ys[t % 5]] = 2.0 ** rng.integers(0, 3, (B, Hkv))
+    return q, k, v, wd, wu, dout
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,d,dd,r", [(1, 2, 2, 10, 64, 16, 16), (2, 8, 2, 140, 64, 64, 0),
+                                               (1, 4, 4, 60, 128, 32, 16), (1, 4, 1, 30, 128, 64, 2),
+                                               (2, 2, 2, 11, 128, 73, 16)])
+def test_chain_rule_keeps_fp32(B, Hq, Hkv, T, d, dd, r):
+    """The fp32 weight gradients against fp64 with nothing rounded before the
+    chain rule. What is left is fp32: the scale (2^-24), one sum over d or a
+    window of exact terms, and one over at most ten keys of each of B sequences,
+    each rounding at 2^-24 of what it has summed; 2^-20 of the summed magnitudes
+    is sixteen such roundings. A factor cut to 16 significant bits misses it by
+    far (2^-17 of a single term)."""
+    rng = np.random.default_rng(d + dd + T)
+    w = T - 10
+    q, k, v, wd, wu, dout = exact_chain_inputs(rng, B, Hq, Hkv, T, d, dd, w)
+    up = lambda x: torch.from_numpy(x).to(torch.bfloat16).cuda()
+    for x in (q, k, v, wd, wu, dout):
+        assert np.array_equal(torch.from_numpy(x).to(torch.bfloat16).double().numpy(), x)
+    lse = torch.zeros(B, Hq, T, device="cuda")
+    got = dar.dar_attn_prefill_rope_backward(up(q), up(k), up(v), up(wd), up(wu), w,
+                                             dar.Rope(r, n_pos=T), torch.zeros_like(up(q)), lse, up(dout))
+    torch.cuda.synchronize()
+    G, Td, s = Hq // Hkv, T - w, d ** -0.5
+    dwd, dwu = np.zeros_like(wd), np.zeros_like(wu)
+    awd, awu = np.zeros_like(wd), np.zeros_like(wu)
+    for b in range(B):
+        for g in range(Hkv):
+            vd = v[b, g, :Td] @ wd[g] @ wu[g]
+            far = np.arange(T)[:, None] - np.arange(Td)[None, :] >= w
+            u = np.zeros((Td, d))
+            dvd = np.zeros((Td, d))
+            for h in range(g * G, (g + 1) * G):
+                ds = np.where(far, dout[b, h] @ vd.T, 0.0)
+                assert np.array_equal(torch.from_numpy(ds).to(torch.bfloat16).double().numpy(), ds)
+                u += ds.T @ q[b, h]
+                dvd += far.T.astype(float) @ dout[b, h]
+            assert max(np.abs(u).max(), np.abs(dvd).max()) < 2 ** 24
+            u *= s
+            kk, vv, gk, gv = k[b, g, :Td], v[b, g, :Td], u @ wu[g].T, dvd @ wu[g].T
+            ck, cv = kk @ wd[g], vv @ wd[g]
+            dwd[g] += kk.T @ gk + vv.T @ gv
+            dwu[g] += ck.T @ u + cv.T @ dvd
+            agk, agv = np.abs(u) @ np.abs(wu[g]).T, np.abs(dvd) @ np.abs(wu[g]).T
+            awd[g] += np.abs(kk).T @ agk + np.abs(vv).T @ agv
+            awu[g] += np.abs(ck).T @ np.abs(u) + np.abs(cv).T @ np.abs(dvd)
+    for n, a, ref, mag in (("dwd", got[3], dwd, awd), ("dwu", got[4], dwu, awu)):
+        err = np.abs(to_host64(a) - ref)
+        assert (mag > 0).any()
+        worst = (err[mag > 0] / mag[mag > 0]).max()
+        print(n, d, dd, "largest error 2^%.1f of the summed magnitudes" % np.log2(max(worst, 2.0 ** -60)))
+        assert worst <= 2.0 ** -20, (n, worst)
+        assert not err[mag == 0].any(), n
+
+
 def test_offset_positions_and_zero_rotary_dim():
     """Rows at positions 77.. of a longer sequence, and r = 0, whose gradients
     are those of the plain backward (checked against the oracle's)."""
