@@ -784,7 +784,7 @@ void prefill_mfma_kernel(
     const float* __restrict__ knorm, const bf16_t* __restrict__ consts, bf16_t* __restrict__ o,
     float* __restrict__ lse, int Hq, int Hkv, int T, int w, int Tp, int nblk, int BH,
     float c_scale, int q0, int n_rows, int kv0, int Tkv, const bf16_t* __restrict__ wv,
-    const int* __restrict__ seq_lens, int parts, LatCache lc) {
+    const int* __restrict__ seq_lens, int parts, int turn, LatCache lc) {
     constexpr bool ROPE = MODE == kModeRope;
     constexpr bool CACHE = MODE == kModeDense || MODE == kModePaged;
     constexpr bool PAGED = MODE == kModePaged;
@@ -807,7 +807,9 @@ void prefill_mfma_kernel(
     // With two parts a workgroup takes row blocks p and nblk-1-p of one (batch,
     // head): a short and a long causal row block, so every workgroup has the
     // same work. With one part (launch_dd: grids that leave the chip room) it
-    // takes block nblk-1-p alone.
+    // takes block nblk-1-p alone, longest first; `turn` workgroups into the grid
+    // (one on every compute unit) the order turns round, so that the second
+    // workgroup of a unit is short where its first is long.
     // Workgroups are dealt to the 8 XCDs round-robin; when BH % 8 == 0 all
     // workgroups of a head are placed on one XCD so its L2 holds only the
     // K/V/latents of BH/8 heads.
@@ -816,14 +818,18 @@ void prefill_mfma_kernel(
     const int BG = BH / G;  // (batch, KV head) groups
     if ((BG & 7) == 0) {
         // the G query heads of a KV head share its XCD (and its L2)
-        const int xcd = wg_id_x() & 7, local = wg_id_x() >> 3;
         const int hpx = BH >> 3;  // query heads per XCD
+        const int xcd = wg_id_x() & 7;
+        int local = wg_id_x() >> 3;
+        if (local >= turn >> 3) local = nblk * hpx - 1 - (local - (turn >> 3));
         pair = local / hpx;
         const int rem = local - pair * hpx;
         bh = ((rem / G) * 8 + xcd) * G + rem % G;
     } else {
-        pair = wg_id_x() / BH;
-        bh = wg_id_x() - pair * BH;
+        int L = wg_id_x();
+        if (L >= turn) L = nblk * BH - 1 - (L - turn);
+        pair = L / BH;
+        bh = L - pair * BH;
     }
     const int b = bh / Hq, h = bh - (bh / Hq) * Hq;
     const int g = h / (Hq / Hkv);
@@ -1165,17 +1171,29 @@ static hipError_t launch_dd(int B, int Hq, int Hkv, const PrefillGeo& geo, int w
     const int T = geo.total();
     const int nblk = (geo.n_rows + BM - 1) / BM;
     const int BH = B * Hq;
-    // One row block per workgroup while all of them are resident at once (two
-    // workgroups on each of 256 compute units: LDS and registers): the longest
-    // block is then the whole time, and pairing would put a second block behind
-    // it on a chip that is partly idle (B1 H8 T331 d64 w128, with the
-    // pre-pass: 19.4 us as pairs, 17.0 alone). Past that, pairs even out the
-    // causal work (B8 H8 T2048 d64 w256 has 1024 blocks: 44 us as pairs).
-    const int parts = (long long)nblk * BH <= 2 * 256 ? 1 : 2;
+    const size_t lds = sizeof(bf16_t) * (4 * 64 * (D + 8) + (wv ? 2 : 1) * DD * (D + 8));
+    // One row block per workgroup while all of them are resident at once: the
+    // longest block is then the whole time, and pairing would put a second block
+    // behind it on a chip that is partly idle (B1 H8 T331 d64 w128, with the
+    // pre-pass: 19.4 us as pairs, 17.0 alone). Where a compute unit holds two
+    // workgroups (registers allow it; LDS all but the shared latents at d = 128,
+    // d_down = 32, 87 KB) that is 512 blocks, and the second 256 go shortest
+    // first, which gives every unit the work of a pair with both blocks in
+    // flight (w256, pairs / longest first throughout / turned: B1 H8 T8192 d64
+    // 64.4 / 62.3 / 56.5 us, B1 H2 T32768 d128 d_down32 270 / 364 / 259 us).
+    // Where it holds one, a unit takes its second block when its first is done,
+    // so longest first is the right order throughout, and pairs win once they
+    // fill the chip (shared latents, d = 128, d_down = 32, pairs / alone: 448
+    // blocks 92.0 / 89.2 and 55.6 / 55.9 us, 512 blocks 100.4 / 104.2 and 58.2 /
+    // 60.0 us). Past that, pairs even out the causal work (B8 H8 T2048 d64 w256
+    // has 1024 blocks: 44 us as pairs).
+    constexpr int kUnits = 256;
+    const bool two = 2 * lds <= 160 * 1024;
+    const int parts = (long long)nblk * BH <= (two ? 2 * kUnits : 2 * kUnits - kUnits / 4) ? 1 : 2;
+    const int turn = parts == 1 && two ? kUnits : 1 << 30;
     const int npair = parts == 1 ? nblk : (nblk + 1) / 2;
     const int Tp = ROPE ? round_up(T - w > 0 ? T - w : 0, 32) : prefill_tp(T, w);
     const float c_scale = 1.4426950408889634f / sqrtf((float)D);
-    const size_t lds = sizeof(bf16_t) * (4 * 64 * (D + 8) + (wv ? 2 : 1) * DD * (D + 8));
     auto kern = prefill_mfma_kernel<D, DD, NW, MODE>;
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1185,7 +1203,7 @@ static hipError_t launch_dd(int B, int Hq, int Hkv, const PrefillGeo& geo, int w
                        (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)wd, (const bf16_t*)wu,
                        (const bf16_t*)cK, (const bf16_t*)cVt, cnorm, knorm, (const bf16_t*)consts,
                        (bf16_t*)o, lse, Hq, Hkv, T, w, Tp, nblk, BH, c_scale, geo.q0,
-                       geo.n_rows, geo.kv0, geo.Tkv, (const bf16_t*)wv, geo.seq_lens, parts, lc);
+                       geo.n_rows, geo.kv0, geo.Tkv, (const bf16_t*)wv, geo.seq_lens, parts, turn, lc);
     return hipGetLastError();
 }
 

@@ -28,6 +28,48 @@ def test_row_blocks_alone_and_in_pairs(B, H, T):
         assert np.abs(o[b, h] - ref).max() <= tol("bf16"), (b, h)
 
 
+@pytest.mark.parametrize("B,H,T", [(3, 33, 512), (1, 51, 1100), (2, 24, 1000), (1, 257, 100), (1, 32, 1100)])
+def test_second_half_of_the_grid_in_turned_order(B, H, T):
+    """256 to 512 blocks: the workgroups from the 257th on take the remaining
+    blocks shortest first, with the heads dealt to the XCDs (a multiple of eight)
+    and without, even and odd block counts, one block past the line. Rows that no
+    workgroup takes, or that two do, show against the same call with the batch
+    and heads cut to grids of at most 256 blocks, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(T)
+    q, k, v = (torch.randn(B, H, T, 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    wd = (torch.randn(H, 64, 16, generator=g, device="cuda") / 8).to(torch.bfloat16)
+    nblk = (T + 127) // 128
+    assert 256 < nblk * B * H <= 512
+    o = torch.full_like(q, float("nan"))
+    dar.dar_attn_prefill(q, k, v, wd, None, 70, o=o)
+    n = 16 if H % 16 == 0 else 17
+    for b in range(B):
+        for h in range(0, H, n):
+            s = slice(h, min(h + n, H))
+            part = dar.dar_attn_prefill(*(x[b:b + 1, s].contiguous() for x in (q, k, v)),
+                                        wd[s].contiguous(), None, 70)
+            assert torch.equal(o[b:b + 1, s].view(torch.int16), part.view(torch.int16)), (b, h)
+
+
+@pytest.mark.parametrize("H,T", [(30, 1100), (56, 1024), (57, 1000), (64, 1000), (65, 1000)])
+def test_shared_latents_one_workgroup_a_unit(H, T):
+    """Shared latents at d = 128, d_down = 32 hold a compute unit's LDS alone:
+    one block each up to 448 blocks, pairs past that (on both sides of the line
+    and of 512)."""
+    d, dd, w = 128, 32, 70
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn(1, H, T, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    c = torch.randn(1, H, T, dd, generator=g, device="cuda").to(torch.bfloat16)
+    uk, uv = ((torch.randn(H, dd, d, generator=g, device="cuda") / 6).to(torch.bfloat16) for _ in range(2))
+    o = torch.full_like(q, float("nan"))
+    dar.dar_attn_prefill_shared(q, k, v, c, uk, uv, w, o=o)
+    for h in range(0, H, 13):
+        s = slice(h, min(h + 13, H))
+        part = dar.dar_attn_prefill_shared(*(x[:, s].contiguous() for x in (q, k, v, c)),
+                                           uk[s].contiguous(), uv[s].contiguous(), w)
+        assert torch.equal(o[:, s].view(torch.int16), part.view(torch.int16)), h
+
+
 def test_rotary_rows_in_one_or_two_launches():
     """Queries and keys are rotated in one launch while their heads fit its
     grid (65535): past that, in two; the same rows come out either way."""
