@@ -448,54 +448,93 @@ __global__ __launch_bounds__(256) void prefill_latent_mfma_kernel(
     }
 }
 
-// One new token per lane column (both lane halves) of a matrix-core append: the
-// leaving rows rk, rv (project) are projected into ok, ov, the new rows nk, nv
-// (to_ring) go to the ring rows dk, dv. All rows are requested before any is
-// used or stored (keys, then values, each after the other's stores, a
-// one-token append was a chain of five memory round trips: 7.3 us at B4 Hkv8
-// in pages, 5.9 so), and a ring
-// slot is read before it is rewritten by the same lane. Row pointers are valid
-// whatever the flags.
-template <int D>
-__device__ __forceinline__ void append_token(const lbf16x8 (&wa)[D / 16], const bf16_t* rk,
-                                             const bf16_t* rv, const bf16_t* nk, const bf16_t* nv,
-                                             bf16_t* ok, bf16_t* ov, bf16_t* dk, bf16_t* dv, int dd,
-                                             int hg, bool project, bool any_project, bool to_ring) {
+// One new token per lane column (both lane halves) of a matrix-core append.
+// Element offsets: `row` of the leaving row (in the ring if old, else among the
+// new ones), projected to `out` (project; any_project: uniform, some lane may);
+// `src` of the new row, which goes to `dst` of the ring (to_ring). They are valid
+// whatever the flags, and a ring slot is read before it is rewritten by the same
+// lane. AHEAD: all four rows are requested before any is used or stored;
+// otherwise one row at a time (append_ahead says when).
+template <int D, bool AHEAD>
+__device__ __forceinline__ void append_token(const lbf16x8 (&wa)[D / 16], const bf16_t* k_new,
+                                             const bf16_t* v_new, bf16_t* k_win, bf16_t* v_win,
+                                             bf16_t* k_out, bf16_t* v_out, bool old, size_t row,
+                                             size_t src, size_t dst, size_t out, int dd, int hg,
+                                             bool project, bool any_project, bool to_ring) {
     constexpr int KS = D / 16;
-    lbf16x8 xk[KS], xv[KS], yk[KS], yv[KS];
+    auto load = [&](lbf16x8 (&x)[KS], const bf16_t* p) {
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        yk[s] = lload8(nk + s * 16 + hg * 8);
-        yv[s] = lload8(nv + s * 16 + hg * 8);
-    }
-    if (any_project) {  // uniform
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            xk[s] = lload8(rk + s * 16 + hg * 8);
-            xv[s] = lload8(rv + s * 16 + hg * 8);
-        }
+        for (int s = 0; s < KS; ++s) x[s] = lload8(p + s * 16 + hg * 8);
+    };
+    auto latent = [&](lbf16x8 (&x)[KS]) {
 #pragma unroll
         for (int s = 0; s < KS; ++s)
-            if (!project) xk[s] = xv[s] = __builtin_bit_cast(lbf16x8, make_uint4(0, 0, 0, 0));
-        const lf32x16 ak = project_mfma<D>(wa, xk), av = project_mfma<D>(wa, xv);
-        if (project) {
+            if (!project) x[s] = __builtin_bit_cast(lbf16x8, make_uint4(0, 0, 0, 0));
+        return project_mfma<D>(wa, x);
+    };
+    auto put = [&](bf16_t* p, const lbf16x8 (&y)[KS]) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int c = acc_col(r, hg);
-                if (c < dd) {
-                    ok[c] = f32_to_bf16(ak[r]);
-                    ov[c] = f32_to_bf16(av[r]);
+        for (int s = 0; s < KS; ++s) *reinterpret_cast<lbf16x8*>(p + s * 16 + hg * 8) = y[s];
+    };
+    if constexpr (AHEAD) {
+        lbf16x8 xk[KS], xv[KS], yk[KS], yv[KS];
+        load(yk, k_new + src);
+        load(yv, v_new + src);
+        if (any_project) {
+            load(xk, (old ? k_win : k_new) + row);
+            load(xv, (old ? v_win : v_new) + row);
+            const lf32x16 ak = latent(xk), av = latent(xv);
+            if (project) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int c = acc_col(r, hg);
+                    if (c < dd) {
+                        k_out[out + c] = f32_to_bf16(ak[r]);
+                        v_out[out + c] = f32_to_bf16(av[r]);
+                    }
                 }
             }
         }
-    }
-    if (to_ring) {
+        if (to_ring) {
+            put(k_win + dst, yk);
+            put(v_win + dst, yv);
+        }
+    } else {
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            *reinterpret_cast<lbf16x8*>(dk + s * 16 + hg * 8) = yk[s];
-            *reinterpret_cast<lbf16x8*>(dv + s * 16 + hg * 8) = yv[s];
+        for (int which = 0; which < 2; ++which) {
+            const bf16_t* fresh = which ? v_new : k_new;
+            bf16_t* ring = which ? v_win : k_win;
+            lbf16x8 x[KS];
+            if (any_project) {
+                load(x, (old ? ring : fresh) + row);
+                const lf32x16 acc = latent(x);
+                bf16_t* p = (which ? v_out : k_out) + out;
+                if (project) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int c = acc_col(r, hg);
+                        if (c < dd) p[c] = f32_to_bf16(acc[r]);
+                    }
+                }
+            }
+            if (to_ring) {
+                load(x, fresh + src);
+                put(ring + dst, x);
+            }
         }
     }
+}
+
+// Rows are requested ahead while the chip has a SIMD for every wavefront (1024)
+// and fewer than 32 tokens for each: with one row after the other's stores a
+// wavefront alone on its SIMD waits for a chain of memory round trips (d = 128,
+// d_down = 32, one token, B32 Hkv8: 6.7 us ahead, 7.8 in turn; 256 tokens, B8
+// Hkv8: 10.4 and 11.2). Past that the other wavefronts cover the round trips, and
+// the registers of four rows (180 against 88) cost the occupancy that does (256
+// tokens, B16 Hkv8: 17.9 and 16.8; 700 tokens, B8 Hkv16: 39.5 and 32.3; 20000
+// tokens, B1 Hkv8: 49.9 and 40.7; one token, B128 Hkv32: 19.5 and 15.4).
+static bool append_ahead(long long waves, long long tokens) {
+    return waves <= 1024 && tokens < 32 * 1024;
 }
 
 // Cache append for bf16 with the matrix-core projection. One wavefront per 32
@@ -503,7 +542,7 @@ __device__ __forceinline__ void append_token(const lbf16x8 (&wa)[D / 16], const 
 // reads elements [16s + 8hg, +8) of the token leaving ring slot p % w is the
 // lane that writes the same elements of the new token into that slot, after
 // its read, so mode 0 needs no barrier.
-template <int D>
+template <int D, bool AHEAD>
 __global__ __launch_bounds__(64) void append_mfma_kernel(
     const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new, const bf16_t* __restrict__ wd,
     bf16_t* k_win, bf16_t* v_win, bf16_t* __restrict__ k_lat, bf16_t* __restrict__ v_lat, int Hkv,
@@ -526,9 +565,8 @@ __global__ __launch_bounds__(64) void append_mfma_kernel(
     const size_t src = (new0 + (to_ring ? tt : 0)) * D;
     const size_t dst = to_ring ? (ring0 + (len + tt) % w) * D : 0;
     const size_t out = project ? ((size_t)bg * cap + ex) * dd : 0;
-    append_token<D>(wa, (old ? k_win : k_new) + row, (old ? v_win : v_new) + row, k_new + src,
-                    v_new + src, k_lat + out, v_lat + out, k_win + dst, v_win + dst, dd, hg, project,
-                    mode != 2, to_ring);
+    append_token<D, AHEAD>(wa, k_new, v_new, k_win, v_win, k_lat, v_lat, old, row, src, dst, out, dd, hg,
+                           project, mode != 2, to_ring);
 }
 
 // The matrix-core projection is used exactly on the shapes the matrix-core
@@ -615,7 +653,9 @@ hipError_t launch_append<bf16_t>(const bf16_t* k_new, const bf16_t* v_new, const
     if (!mfma_projection(d, dd))
         return launch_append_valu<bf16_t>(k_new, v_new, wd, k_win, v_win, k_lat, v_lat, B, Hkv, d, dd, w, cap, len, n, st);
     dim3 grid((n + 31) / 32, B * Hkv);
-    auto kern = (d == 64) ? append_mfma_kernel<64> : append_mfma_kernel<128>;
+    const bool ahead = append_ahead((long long)grid.x * grid.y, (long long)n * grid.y);
+    auto kern = d == 64 ? (ahead ? append_mfma_kernel<64, true> : append_mfma_kernel<64, false>)
+                        : (ahead ? append_mfma_kernel<128, true> : append_mfma_kernel<128, false>);
     if (n <= w || w == 0) {
         hipLaunchKernelGGL(kern, grid, dim3(64), 0, st, k_new, v_new, wd, k_win, v_win, k_lat, v_lat, Hkv, dd, w, cap, len, n, 0);
         return hipGetLastError();
@@ -756,7 +796,7 @@ namespace dar {
 // (matrix cores: token in column 0), then the new token goes to ring slot
 // len % w (after the read of the same slot). A sequence at capacity, or whose
 // page is not mapped, stores nothing.
-template <int D>
+template <int D, bool AHEAD>
 __global__ __launch_bounds__(64) void append_paged_mfma_kernel(
     const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new, const bf16_t* __restrict__ wd,
     bf16_t* k_win, bf16_t* v_win, bf16_t* __restrict__ k_pool, bf16_t* __restrict__ v_pool,
@@ -780,9 +820,8 @@ __global__ __launch_bounds__(64) void append_paged_mfma_kernel(
     const size_t row = old ? ((size_t)bg * w + ex % w) * D : src;
     const size_t dst = w > 0 ? ((size_t)bg * w + len % w) * D : 0;
     const size_t out = project ? (((size_t)page * Hkv + g) * pg.ps + ex % pg.ps) * dd : 0;
-    append_token<D>(wa, (old ? k_win : k_new) + row, (old ? v_win : v_new) + row, k_new + src,
-                    v_new + src, k_pool + out, v_pool + out, k_win + dst, v_win + dst, dd, hg,
-                    project && tl == 0, project, w > 0 && tl == 0);
+    append_token<D, AHEAD>(wa, k_new, v_new, k_win, v_win, k_pool, v_pool, old, row, src, dst, out, dd, hg,
+                           project && tl == 0, project, w > 0 && tl == 0);
 }
 
 // The same for every dtype and head size, on the vector ALUs (project_col:
@@ -833,7 +872,9 @@ hipError_t launch_append_paged(const T* k_new, const T* v_new, const T* wd, T* k
                                T* k_pool, T* v_pool, const PagedArgs& pg, int* lens, int B, int Hkv,
                                int d, int dd, int w, hipStream_t st) {
     if (sizeof(T) == 2 && mfma_projection(d, dd)) {
-        auto kern = d == 64 ? append_paged_mfma_kernel<64> : append_paged_mfma_kernel<128>;
+        const bool ahead = append_ahead((long long)B * Hkv, (long long)B * Hkv);
+        auto kern = d == 64 ? (ahead ? append_paged_mfma_kernel<64, true> : append_paged_mfma_kernel<64, false>)
+                            : (ahead ? append_paged_mfma_kernel<128, true> : append_paged_mfma_kernel<128, false>);
         hipLaunchKernelGGL(kern, dim3(B * Hkv), dim3(64), 0, st, (const bf16_t*)k_new,
                            (const bf16_t*)v_new, (const bf16_t*)wd, (bf16_t*)k_win, (bf16_t*)v_win,
                            (bf16_t*)k_pool, (bf16_t*)v_pool, pg, Hkv, dd, w);
@@ -1027,7 +1068,7 @@ hipError_t launch_chunk_gather_paged(const bf16_t* k_win, const bf16_t* v_win, c
 // project and ring, safe when n <= w: the lane that reads a ring slot is the
 // one that rewrites it; 1: project only; 2: ring only). The window exit of
 // new token tt is position lens[b] + tt - w, written to its page slot.
-template <int D>
+template <int D, bool AHEAD>
 __global__ __launch_bounds__(64) void append_chunk_paged_mfma_kernel(
     const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new, const bf16_t* __restrict__ wd,
     bf16_t* k_win, bf16_t* v_win, bf16_t* __restrict__ k_pool, bf16_t* __restrict__ v_pool, LatCache lc,
@@ -1054,9 +1095,8 @@ __global__ __launch_bounds__(64) void append_chunk_paged_mfma_kernel(
     const size_t src = (new0 + (to_ring ? tt : 0)) * D;
     const size_t dst = to_ring ? (ring0 + (L + tt) % w) * D : 0;
     const size_t out = project ? (((((size_t)page) * Hkv + g) << lc.ps_shift) + (ex & ((1 << lc.ps_shift) - 1))) * dd : 0;
-    append_token<D>(wa, (old ? k_win : k_new) + row, (old ? v_win : v_new) + row, k_new + src,
-                    v_new + src, k_pool + out, v_pool + out, k_win + dst, v_win + dst, dd, hg, project,
-                    mode != 2, to_ring);
+    append_token<D, AHEAD>(wa, k_new, v_new, k_win, v_win, k_pool, v_pool, old, row, src, dst, out, dd, hg,
+                           project, mode != 2, to_ring);
 }
 
 hipError_t launch_append_chunk_paged(const bf16_t* k_new, const bf16_t* v_new, const bf16_t* wd,
@@ -1065,7 +1105,9 @@ hipError_t launch_append_chunk_paged(const bf16_t* k_new, const bf16_t* v_new, c
                                      hipStream_t st) {
     if (!mfma_projection(d, dd)) return hipErrorNotSupported;
     dim3 grid((n + 31) / 32, B * Hkv);
-    auto kern = (d == 64) ? append_chunk_paged_mfma_kernel<64> : append_chunk_paged_mfma_kernel<128>;
+    const bool ahead = append_ahead((long long)grid.x * grid.y, (long long)n * grid.y);
+    auto kern = d == 64 ? (ahead ? append_chunk_paged_mfma_kernel<64, true> : append_chunk_paged_mfma_kernel<64, false>)
+                        : (ahead ? append_chunk_paged_mfma_kernel<128, true> : append_chunk_paged_mfma_kernel<128, false>);
     if (n <= w || w == 0) {
         hipLaunchKernelGGL(kern, grid, dim3(64), 0, st, k_new, v_new, wd, k_win, v_win, k_pool, v_pool, lc, Hkv,
                            dd, w, n, 0);
