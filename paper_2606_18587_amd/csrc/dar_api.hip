@@ -127,13 +127,34 @@ bool group_supported(const dar_shape* s) {
 
 void clear_hip_error() { (void)hipGetLastError(); }
 
+// The kernel family of a prefill or backward, chosen once for the log and the
+// launch: bf16 on the matrix cores, fp32 on the fp32 matrix cores, or the
+// vector-ALU kernels that take every shape.
+enum class Path { kValu, kMfma, kF32Mfma };
+
+const char* path_name(Path p) {
+    return p == Path::kMfma ? "mfma" : p == Path::kF32Mfma ? "f32_mfma" : "valu";
+}
+
+Path prefill_path(const dar_shape* s) {
+    if (prefill_mfma_supported(s)) return Path::kMfma;
+    return s->dtype == DAR_F32 && f32_mfma_supported(s->d, s->d_down) ? Path::kF32Mfma : Path::kValu;
+}
+
+Path backward_path(const dar_shape* s) {
+    if (env_flag("DAR_BWD_VALU")) return Path::kValu;
+    if (bwd_mfma_supported(s->d, s->d_down, s->dtype == DAR_BF16)) return Path::kMfma;
+    return s->dtype == DAR_F32 && f32_mfma_supported(s->d, s->d_down) ? Path::kF32Mfma : Path::kValu;
+}
+
 // Pre-pass and attention kernels of one prefill (whole sequence or chunk):
 // k and v hold the positions geo describes, ws the prefill workspace laid out
 // as L for geo.total() positions.
 hipError_t run_prefill(const dar_shape* s, const PrefillGeo& geo, const void* q, const void* k,
                        const void* v, const void* w_down, const void* w_up, void* o, float* lse,
-                       void* ws, const PrefillWs& L, bool fast, hipStream_t stream,
+                       void* ws, const PrefillWs& L, Path path, hipStream_t stream,
                        const void* w_val = nullptr) {
+    const bool fast = path == Path::kMfma;
     char* wsb = (char*)ws;
     void* cK = wsb + L.ck_off;
     void* cV = wsb + L.cv_off;
@@ -160,7 +181,7 @@ hipError_t run_prefill(const dar_shape* s, const PrefillGeo& geo, const void* q,
                                      (float*)cK, (float*)cV, cnorm, knorm, (float*)consts, s->B,
                                      s->Hkv, geo, s->d, s->d_down, s->w, false, stream);
     if (e != hipSuccess) return e;
-    if (f32_mfma_supported(s->d, s->d_down))
+    if (path == Path::kF32Mfma)
         return launch_prefill_f32((const float*)q, (const float*)k, (const float*)v,
                                   (const float*)w_down, (const float*)w_up, (const float*)cK,
                                   (const float*)cV, (float*)o, lse, s->B, s->Hq, s->Hkv, geo, s->d,
@@ -445,17 +466,13 @@ dar_status dar_attn_prefill_lse(const dar_shape* s, int T, const void* q, const 
     if (!aligned16(ws)) return DAR_E_ARG;
 
     clear_hip_error();
-    hipError_t e = hipSuccess;
-    const bool fast = prefill_mfma_supported(s);
+    const Path path = prefill_path(s);
     if (log_enabled())
         fprintf(stderr, "[dar] prefill B=%d Hq=%d Hkv=%d T=%d d=%d dd=%d w=%d %s path=%s\n", s->B,
                 s->Hq, s->Hkv, T, s->d, s->d_down, s->w, s->dtype == DAR_BF16 ? "bf16" : "f32",
-                fast ? "mfma" : "valu");
-    if (s->dtype == DAR_BF16) {
-        e = run_prefill(s, whole_sequence(T), q, k, v, w_down, w_up, o, lse, ws, L, fast, stream);
-    } else {
-        e = run_prefill(s, whole_sequence(T), q, k, v, w_down, w_up, o, lse, ws, L, false, stream);
-    }
+                path_name(path));
+    const hipError_t e =
+        run_prefill(s, whole_sequence(T), q, k, v, w_down, w_up, o, lse, ws, L, path, stream);
     return e == hipSuccess ? DAR_OK : DAR_E_HIP;
 }
 
@@ -475,8 +492,8 @@ dar_status dar_attn_prefill_ragged(const dar_shape* s, int T, const int* seq_len
     clear_hip_error();
     PrefillGeo geo = whole_sequence(T);
     geo.seq_lens = seq_lens;
-    const bool fast = s->dtype == DAR_BF16 && prefill_mfma_supported(s);
-    const hipError_t e = run_prefill(s, geo, q, k, v, w_down, w_up, o, lse, ws, L, fast, stream);
+    const hipError_t e =
+        run_prefill(s, geo, q, k, v, w_down, w_up, o, lse, ws, L, prefill_path(s), stream);
     return e == hipSuccess ? DAR_OK : DAR_E_HIP;
 }
 
@@ -501,16 +518,14 @@ dar_status dar_attn_prefill_backward(const dar_shape* s, int T, const void* q, c
     if (!aligned16(ws)) return DAR_E_ARG;
 
     clear_hip_error();
+    const Path path = backward_path(s);
     if (log_enabled())
         fprintf(stderr, "[dar] prefill_backward B=%d Hq=%d Hkv=%d T=%d d=%d dd=%d w=%d %s path=%s\n",
                 s->B, s->Hq, s->Hkv, T, s->d, s->d_down, s->w, s->dtype == DAR_BF16 ? "bf16" : "f32",
-                bwd_mfma_supported(s->d, s->d_down, s->dtype == DAR_BF16) && !env_flag("DAR_BWD_VALU")
-                    ? "mfma" : "valu");
+                path_name(path));
     hipError_t e;
-    const bool fast = bwd_mfma_supported(s->d, s->d_down, s->dtype == DAR_BF16) &&
-                      !env_flag("DAR_BWD_VALU");
-    const BwdWs L = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, fast);
-    if (fast)
+    const BwdWs L = bwd_ws_layout(s->B, s->Hq, s->Hkv, T, s->d, s->d_down, path == Path::kMfma);
+    if (path == Path::kMfma)
         e = launch_bwd_mfma((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)o,
                             lse, (const bf16_t*)dout, (const bf16_t*)w_down, (const bf16_t*)w_up,
                             (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, dw_down, dw_up, (char*)ws, L,
@@ -521,7 +536,7 @@ dar_status dar_attn_prefill_backward(const dar_shape* s, int T, const void* q, c
                                     (const bf16_t*)w_up, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv,
                                     dw_down, dw_up, (char*)ws, L, s->B, s->Hq, s->Hkv, T, s->d,
                                     s->d_down, s->w, stream);
-    else if (f32_mfma_supported(s->d, s->d_down) && !env_flag("DAR_BWD_VALU"))
+    else if (path == Path::kF32Mfma)
         e = launch_bwd_f32((const float*)q, (const float*)k, (const float*)v, (const float*)o, lse,
                            (const float*)dout, (const float*)w_down, (const float*)w_up, (float*)dq,
                            (float*)dk, (float*)dv, dw_down, dw_up, (char*)ws, L, s->B, s->Hq,
@@ -594,7 +609,6 @@ dar_status dar_attn_prefill_chunk(const dar_shape* s, dar_cache* c, int n, const
     // rows len..len+n-1; keys/values from the context rows; latents of the
     // tokens that left the window before this chunk from the cache
     const PrefillGeo geo{len, n, L.kv0, L.Tc, L.kv0, c->cap, c->k_lat, c->v_lat};
-    const bool fast = prefill_mfma_supported(s);
     hipError_t e;
     if (s->dtype == DAR_BF16)
         e = launch_chunk_gather<bf16_t>((const bf16_t*)c->k_win, (const bf16_t*)c->v_win,
@@ -608,7 +622,7 @@ dar_status dar_attn_prefill_chunk(const dar_shape* s, dar_cache* c, int n, const
                                        stream);
     if (e == hipSuccess)
         e = run_prefill(s, geo, q, ctx_k, ctx_v, w_down, w_up, o, lse, wsb + L.pre_off, L.pre,
-                        fast, stream);
+                        prefill_path(s), stream);
     // the cache update is the append of the same tokens (the attention above
     // reads only the context copy and the workspace)
     if (e == hipSuccess) {
@@ -892,12 +906,12 @@ dar_status dar_attn_prefill_shared(const dar_shape* s, int T, const void* q, con
     // W_down operand is never used for a projection here (U_K, of the same
     // size, is passed so that its loads stay in bounds).
     const PrefillGeo geo{0, T, 0, T, T, T, c, c};
-    const bool fast = s->dtype == DAR_BF16 && prefill_mfma_supported(s);
+    const Path path = prefill_path(s);
     if (log_enabled())
         fprintf(stderr, "[dar] prefill_shared B=%d Hq=%d Hkv=%d T=%d d=%d dd=%d w=%d %s path=%s\n",
                 s->B, s->Hq, s->Hkv, T, s->d, s->d_down, s->w, s->dtype == DAR_BF16 ? "bf16" : "f32",
-                fast ? "mfma" : "valu");
-    const hipError_t e = run_prefill(s, geo, q, k, v, u_k, u_k, o, lse, ws, L, fast, stream, u_v);
+                path_name(path));
+    const hipError_t e = run_prefill(s, geo, q, k, v, u_k, u_k, o, lse, ws, L, path, stream, u_v);
     return e == hipSuccess ? DAR_OK : DAR_E_HIP;
 }
 

@@ -8,6 +8,8 @@ address to a kernel.
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -651,3 +653,35 @@ def test_bench_refuses_several_gpus():
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 2
     assert "one GPU" in r.stderr
+
+
+@no_gpu
+def test_log_names_the_kernels_that_run():
+    """DAR_LOG=1 names the kernel family of a prefill, a shared-latent prefill and
+    a backward (DAR_BWD_VALU, read at each call, forces the last); without a GPU
+    the launch after the line fails, in a process of its own."""
+    shapes = [("bfloat16", 64, 16, "mfma"), ("bfloat16", 80, 16, "valu"), ("float32", 64, 16, "f32_mfma"),
+              ("float32", 128, 32, "f32_mfma"), ("float32", 128, 33, "valu"), ("float32", 256, 16, "valu")]
+    code = """
+import ctypes, os, sys, torch
+sys.path.insert(0, %r)
+import paper_2606_18587_amd as dar
+assert not torch.cuda.is_available()
+F = ctypes.c_void_p(1 << 20)
+for dtype, d, dd, _ in %r:
+    r = ctypes.byref(dar.make_shape(1, 1, 1, d, dd, 4, getattr(torch, dtype)))
+    bwd = lambda: dar.lib.dar_attn_prefill_backward(r, 8, F, F, F, F, None, F, F, F, F, F, F, F, None, F,
+                                                    1 << 30, None)
+    assert dar.lib.dar_attn_prefill(r, 8, F, F, F, F, None, F, F, 1 << 30, None) == dar.DAR_E_HIP
+    assert dar.lib.dar_attn_prefill_shared(r, 8, F, F, F, F, F, F, F, None, F, 1 << 30, None) == dar.DAR_E_HIP
+    assert bwd() == dar.DAR_E_HIP
+    os.environ["DAR_BWD_VALU"] = "1"
+    assert bwd() == dar.DAR_E_HIP
+    del os.environ["DAR_BWD_VALU"]
+""" % (ROOT, shapes)
+    env = {k: v for k, v in os.environ.items() if k != "DAR_BWD_VALU"}
+    p = subprocess.run([sys.executable, "-c", code], env=dict(env, DAR_LOG="1"), capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr[-2000:]
+    got = re.findall(r"\[dar\] (\w+) .*path=(\w+)", p.stderr)
+    assert got == [line for *_, want in shapes for line in (
+        ("prefill", want), ("prefill_shared", want), ("prefill_backward", want), ("prefill_backward", "valu"))]
