@@ -290,13 +290,8 @@ RopeBwdWs rope_bwd_ws_layout(const dar_shape* s, int T) {
     put(L.vd, B * Hkv * Td * d * 2);
     put(L.nl2, B * Hq * Tr * 4);
     put(L.nd, B * Hq * Tr * 4);
-    // one share per workgroup of 128 keys; the size asked of the caller stays
-    // that of the fp32 gradient arrays (rows, window and distant keys) and a
-    // share per 32 keys, which contains it: programs hold buffers of that size
-    L.nchunk = (int)B * ((T + 127) / 128);
-    L.wpart = off;
-    off += al(B * Hq * T * d * 4) + 2 * al(B * Hkv * T * d * 4) + 2 * al(B * Hkv * Td * d * 4);
-    off += al(2 * Hkv * B * ((T + 31) / 32) * d * dd * 4);
+    L.nchunk = (int)B * ((T + 127) / 128);  // one share per workgroup of 128 keys
+    put(L.wpart, 2 * Hkv * (size_t)L.nchunk * d * dd * 4);
     L.bytes = off;
     return L;
 }
