@@ -1104,8 +1104,6 @@ dar_status dar_attn_prefill_rope_backward(const dar_shape* s, int T, int pos0, c
     if ((w_up == nullptr) != (dw_up == nullptr)) return DAR_E_ARG;
     if (dw_up && !aligned16(dw_up)) return DAR_E_ARG;
     if (!bwd_rope_mfma_supported(s->d, s->d_down, s->dtype == DAR_BF16)) return DAR_E_UNSUPPORTED;
-    if ((long long)s->B * ((T + 31) / 32) > 65535) return DAR_E_UNSUPPORTED;
-    if ((long long)s->B * s->Hkv > 65535) return DAR_E_UNSUPPORTED;
     const RopeBwdWs L = rope_bwd_ws_layout(s, T);
     if (ws == nullptr || ws_bytes < L.bytes) return DAR_E_WORKSPACE;
     if (!aligned16(ws)) return DAR_E_ARG;

@@ -228,6 +228,33 @@ def test_offset_positions_and_zero_rotary_dim():
     compare(got, ref, "r=0 against the plain backward")
 
 
+def test_many_short_sequences():
+    """A batch of more than 65535 blocks of 32 keys, in the workspace that is
+    asked for and nothing past it, against the same sequences in two halves: dq,
+    dk and dv bit for bit, dW_down as their fp32 sum."""
+    B, T, d, dd, w, r = 2100, 1000, 64, 16, 900, 16
+    assert B * ((T + 31) // 32) > 65535
+    g = torch.Generator(device="cuda").manual_seed(8)
+    q, k, v, dout = (torch.randn(B, 1, T, d, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    wd = (torch.randn(1, d, dd, generator=g, device="cuda") / 8).to(torch.bfloat16)
+    rope = dar.Rope(r, n_pos=T)
+
+    def grads(s, ws=None):
+        x = [t[s] for t in (q, k, v, dout)]
+        o, lse = dar.dar_attn_prefill_rope(*x[:3], wd, None, w, rope, return_lse=True)
+        return dar.dar_attn_prefill_rope_backward(*x[:3], wd, None, w, rope, o, lse, x[3], ws=ws)
+
+    need = dar.dar_prefill_rope_backward_workspace_bytes(dar.make_shape(B, 1, 1, d, dd, w, torch.bfloat16), T)
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    whole = grads(slice(None), ws[:need])
+    assert bool((ws[need:] == 0x5A).all())
+    halves = [grads(slice(0, B // 2)), grads(slice(B // 2, B))]
+    for n in range(3):
+        for s, h in zip((slice(0, B // 2), slice(B // 2, B)), halves):
+            assert torch.equal(whole[n][s].view(torch.int16), h[n].view(torch.int16))
+    torch.testing.assert_close(whole[3], halves[0][3] + halves[1][3], rtol=1e-4, atol=1e-4 * float(whole[3].abs().max()))
+
+
 def test_deterministic():
     wl = BF16_SMALL.with_(w=64, T=333, B=2)
     inp = di.make_backward_inputs(wl, untied=True)
