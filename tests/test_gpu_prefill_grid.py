@@ -70,6 +70,50 @@ def test_shared_latents_one_workgroup_a_unit(H, T):
         assert torch.equal(o[:, s].view(torch.int16), part.view(torch.int16)), h
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d,dd,w", [(64, 16, 100), (128, 32, 300), (64, 32, 0)])
+def test_large_chunks_against_their_sequences(d, dd, w, paged):
+    """A chunk over more than 512 blocks (pairs) and more than 8192 blocks of 32
+    positions (norms of eight blocks a wavefront) against its sequences one by
+    one, which take one block a workgroup and one a wavefront: the same rows,
+    log-sum-exps and cache, bit for bit."""
+    B, H, L, n, page = 9, 8, 4001, 1000, 64
+    assert ((n + 127) // 128) * B * H > 512 and ((L + n + 31) // 32) * B * H > 8192
+    assert ((n + 127) // 128) * H <= 512 and ((L + n + 31) // 32) * H <= 8192
+    g = torch.Generator(device="cuda").manual_seed(d + w)
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    lat, win = [randn(B, H, L, dd) for _ in range(2)], [randn(B, H, max(w, 1), d) for _ in range(2)]
+    q, k, v = (randn(B, H, n, d) for _ in range(3))
+    wd = (torch.randn(H, d, dd, generator=g, device="cuda") * d ** -0.5).to(torch.bfloat16)
+    nb = (L + n + page - 1) // page
+
+    def run(s):
+        m = q[s].shape[0]
+        if paged:
+            c = dar.DarPagedCache(m, H, d, dd, w, page, nb, m * nb, torch.bfloat16)
+            c.block_table.copy_(torch.arange(m * nb, dtype=torch.int32).view(m, nb))
+            c.lens.fill_(L)
+            for pool, x in zip((c.k_pool, c.v_pool), lat):
+                pad = torch.zeros(m, H, nb * page, dd, dtype=torch.bfloat16, device="cuda")
+                pad[:, :, :L] = x[s]
+                pool.copy_(pad.view(m, H, nb, page, dd).transpose(1, 2).reshape(m * nb, H, page, dd))
+        else:
+            c = dar.DarCache(m, H, d, dd, w, L + n, torch.bfloat16)
+            c.struct.len = L
+            c.k_lat[:, :, :L], c.v_lat[:, :, :L] = lat[0][s], lat[1][s]
+        c.k_win.copy_(win[0][s]), c.v_win.copy_(win[1][s])
+        f = dar.dar_attn_prefill_chunk_paged if paged else dar.dar_attn_prefill_chunk
+        o, lse = f(c, q[s].contiguous(), k[s].contiguous(), v[s].contiguous(), wd, return_lse=True)
+        pool = [t.view(m, nb, H, page, dd) for t in (c.k_pool, c.v_pool)] if paged else [c.k_lat, c.v_lat]
+        return [o, lse, c.k_win, c.v_win] + pool
+
+    whole = run(slice(None))
+    assert torch.isfinite(whole[0]).all()
+    for b in range(B):
+        for a, p in zip(whole, run(slice(b, b + 1))):
+            assert torch.equal(a[b:b + 1].view(torch.int16), p.view(torch.int16)), b
+
+
 def test_rotary_rows_in_one_or_two_launches():
     """Queries and keys are rotated in one launch while their heads fit its
     grid (65535): past that, in two; the same rows come out either way."""
