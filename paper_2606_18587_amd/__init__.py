@@ -433,7 +433,7 @@ class DarCache:
 def dar_cache_append(cache: DarCache, k_new, v_new, w_down, Hq=None, stream=None):
     """Append n tokens k_new, v_new [B,Hkv,n,d]; projects window exits to latents."""
     B, Hkv, n, d = k_new.shape
-    key = (B, Hq if Hq is not None else Hkv, Hkv, d, cache.d_down, int(cache.w),
+    key = (B, int(Hq if Hq is not None else Hkv), Hkv, d, int(cache.d_down), int(cache.w),
            k_new.dtype)
     shape = _shape(*key)
     if v_new.shape != (B, Hkv, n, d) or (B, Hkv, d) != (cache.B, cache.Hkv, cache.d):
@@ -457,7 +457,7 @@ def dar_attn_prefill_chunk(cache: DarCache, q, k_new, v_new, w_down, w_up=None, 
     dar_cache_append would. Returns o [B,Hq,n,d], or (o, lse) with return_lse."""
     B, Hq, n, d = q.shape
     Hkv = cache.Hkv
-    key = (B, Hq, Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     if check:
         for name, t in (("k_new", k_new), ("v_new", v_new)):
@@ -494,7 +494,7 @@ def dar_attn_prefill_chunk_rope(cache: DarCache, q, k_new, v_new, w_down, rope: 
     Returns o [B,Hq,n,d], or (o, lse) with return_lse."""
     B, Hq, n, d = q.shape
     Hkv = cache.Hkv
-    key = (B, Hq, Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     if check:
         for name, t in (("k_new", k_new), ("v_new", v_new)):
@@ -523,12 +523,12 @@ def dar_attn_prefill_chunk_rope(cache: DarCache, q, k_new, v_new, w_down, rope: 
 def dar_attn_decode(cache: DarCache, q, w_down, w_up=None, o=None, ws=None, stream=None):
     """One decode step: q [B,Hq,d] at position cache.len - 1. Returns o [B,Hq,d]."""
     B, Hq, d = q.shape
-    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(cache.Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (int(cache.cap),)), q.device)
     st = lib.dar_attn_decode(ctypes.byref(shape), ctypes.byref(cache.struct), _ptr(q),
                              _ptr(w_down), _ptr(w_up), _ptr(o), _ptr(ws),
                              0 if ws is None else ws.numel() * ws.element_size(),
@@ -543,7 +543,7 @@ def dar_attn_decode_noalloc(cache: "DarCache", q, w_down, w_up=None, o=None, str
     no workspace (its partial records live in a fixed array inside the
     library). Pass `o` to keep the call free of allocation."""
     B, Hq, d = q.shape
-    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(cache.Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
@@ -567,12 +567,12 @@ def dar_attn_decode_rope(cache: "DarCache", q, w_down, rope: Rope, w_up=None, o=
     """One decode step with the rotary embedding of Eq. 3; q [B,Hq,d] un-rotated,
     at position cache.len - 1. Returns o [B,Hq,d]."""
     B, Hq, d = q.shape
-    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(cache.Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (int(cache.cap),)), q.device)
     rs = rope.struct()
     st = lib.dar_attn_decode_rope(ctypes.byref(shape), ctypes.byref(cache.struct), ctypes.byref(rs), _ptr(q),
                                   _ptr(w_down), _ptr(w_up), _ptr(o), _ptr(ws),
@@ -616,7 +616,7 @@ def dar_cache_append_shared(cache: DarCache, k_new, v_new, c_new, Hq=None, strea
     """Append n tokens with their shared latents c_new [B,Hkv,n,dd]."""
     assert cache.shared, "a cache made with shared=True"
     B, Hkv, n, d = k_new.shape
-    key = (B, Hq or Hkv, Hkv, d, cache.d_down, int(cache.w), k_new.dtype)
+    key = (B, int(Hq or Hkv), Hkv, d, int(cache.d_down), int(cache.w), k_new.dtype)
     shape = _shape(*key)
     st = lib.dar_cache_append_shared(ctypes.byref(shape), ctypes.byref(cache.struct), _ptr(k_new),
                                      _ptr(v_new), _ptr(c_new), int(n), _stream(stream))
@@ -628,12 +628,12 @@ def dar_attn_decode_shared(cache: DarCache, q, u_k, u_v, o=None, ws=None, stream
     """One decode step over a shared-latent cache; q [B,Hq,d] at position len-1."""
     assert cache.shared, "a cache made with shared=True"
     B, Hq, d = q.shape
-    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(cache.Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (int(cache.cap),)), q.device)
     st = lib.dar_attn_decode_shared(ctypes.byref(shape), ctypes.byref(cache.struct), _ptr(q),
                                     _ptr(u_k), _ptr(u_v), _ptr(o), _ptr(ws),
                                     0 if ws is None else ws.numel() * ws.element_size(),
@@ -680,7 +680,7 @@ class DarPagedCache:
 def dar_cache_append_paged(cache: DarPagedCache, k_new, v_new, w_down, Hq=None, stream=None):
     """One token per sequence: k_new, v_new [B,Hkv,d]; lens advance on the device."""
     B, Hkv, d = k_new.shape
-    key = (B, Hq or Hkv, Hkv, d, cache.d_down, int(cache.w), k_new.dtype)
+    key = (B, int(Hq or Hkv), Hkv, d, int(cache.d_down), int(cache.w), k_new.dtype)
     shape = _shape(*key)
     cs = cache.struct()
     st = lib.dar_cache_append_paged(ctypes.byref(shape), ctypes.byref(cs), _ptr(k_new), _ptr(v_new),
@@ -692,12 +692,12 @@ def dar_cache_append_paged(cache: DarPagedCache, k_new, v_new, w_down, Hq=None, 
 def dar_attn_decode_paged(cache: DarPagedCache, q, w_down, w_up=None, o=None, ws=None, stream=None):
     """One decode step per sequence (query at position lens[b] - 1)."""
     B, Hq, d = q.shape
-    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(cache.Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (int(cache.cap),)), q.device)
     cs = cache.struct()
     st = lib.dar_attn_decode_paged(ctypes.byref(shape), ctypes.byref(cs), _ptr(q), _ptr(w_down),
                                    _ptr(w_up), _ptr(o), _ptr(ws),
@@ -713,12 +713,12 @@ def dar_attn_decode_paged_rope(cache: DarPagedCache, q, w_down, rope: "Rope", w_
     """dar_attn_decode_paged with the rotary embedding of Eq. 3 (query of
     sequence b at position lens[b] - 1; rope.n_pos >= the cache capacity)."""
     B, Hq, d = q.shape
-    key = (B, Hq, cache.Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(cache.Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     if o is None:
         o = torch.empty_like(q)
     if ws is None:
-        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (cache.cap,)), q.device)
+        ws = _workspace(_ws_bytes("dar_decode_workspace_bytes", key, (int(cache.cap),)), q.device)
     cs = cache.struct()
     rs = rope.struct()
     st = lib.dar_attn_decode_paged_rope(ctypes.byref(shape), ctypes.byref(cs), ctypes.byref(rs),
@@ -743,7 +743,7 @@ def dar_attn_prefill_chunk_paged(cache: DarPagedCache, q, k_new, v_new, w_down, 
     Returns o [B,Hq,n,d] (rows past n_new[b] not written), or (o, lse)."""
     B, Hq, n, d = q.shape
     Hkv = cache.Hkv
-    key = (B, Hq, Hkv, d, cache.d_down, int(cache.w), q.dtype)
+    key = (B, Hq, int(Hkv), d, int(cache.d_down), int(cache.w), q.dtype)
     shape = _shape(*key)
     for name, t in (("k_new", k_new), ("v_new", v_new)):
         if t.shape != (B, Hkv, n, d) or t.dtype != q.dtype:
@@ -757,7 +757,7 @@ def dar_attn_prefill_chunk_paged(cache: DarPagedCache, q, k_new, v_new, w_down, 
     if return_lse and lse is None:
         lse = torch.empty(B, Hq, n, dtype=torch.float32, device=q.device)
     if ws is None:
-        ws = _workspace(_ws_bytes("dar_prefill_chunk_paged_workspace_bytes", key, (cache.cap, n)), q.device)
+        ws = _workspace(_ws_bytes("dar_prefill_chunk_paged_workspace_bytes", key, (int(cache.cap), n)), q.device)
     cs = cache.struct()
     st = lib.dar_attn_prefill_chunk_paged(ctypes.byref(shape), ctypes.byref(cs), int(n),
                                           _ptr(n_new), _ptr(q), _ptr(k_new), _ptr(v_new),

@@ -684,3 +684,21 @@ for dtype, d, dd, _ in %r:
     got = re.findall(r"\[dar\] (\w+) .*path=(\w+)", p.stderr)
     assert got == [line for *_, want in shapes for line in (
         ("prefill", want), ("prefill_shared", want), ("prefill_backward", want), ("prefill_backward", "valu"))]
+
+
+@no_gpu
+def test_sizes_may_be_any_integer_like_value():
+    """A head count, latent size or window given as a 0-d array goes through int()
+    before it keys a cached struct or size (such an array cannot be hashed). The
+    call then reaches the library, whose launch fails here."""
+    import numpy as np
+    c = dar.DarCache(1, 2, 64, 16, 4, 32, torch.bfloat16, device="cpu")
+    c.d_down, c.w, c.cap = np.array(16), np.array(4), np.array(32)
+    kv, q = torch.zeros(1, 2, 1, 64, dtype=torch.bfloat16), torch.zeros(1, 4, 64, dtype=torch.bfloat16)
+    wd = torch.zeros(2, 64, 16, dtype=torch.bfloat16)
+    stream = type("S", (), {"cuda_stream": 0})
+    with pytest.raises(dar.DarError):
+        dar.dar_cache_append(c, kv, kv, wd, Hq=np.array(4), stream=stream)
+    c.struct.len = 8
+    with pytest.raises(dar.DarError):
+        dar.dar_attn_decode(c, q, wd, stream=stream)
