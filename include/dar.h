@@ -423,7 +423,7 @@ dar_status dar_attn_prefill_backward(const dar_shape* s, int T, const void* q, c
  *   (caller-owned, overwritten): the rotated and lifted operands, fp32 row
  *   constants and the shares of the weight gradients.
  * Supported: bf16 with d in {64, 128}, any rotary_dim, d_down up to d (up to
- * 64 at d = 128); other shapes return DAR_E_UNSUPPORTED. */
+ * 73 at d = 128); other shapes return DAR_E_UNSUPPORTED. */
 dar_status dar_attn_prefill_rope_backward(const dar_shape* s, int T, int pos0, const dar_rope* rope,
                                           const void* q, const void* k, const void* v,
                                           const void* w_down, const void* w_up, const void* o,

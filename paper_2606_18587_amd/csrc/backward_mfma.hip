@@ -1792,7 +1792,8 @@ hipError_t allow_lds(const void* fn, int bytes) {
 
 }  // namespace
 
-// d_down up to d, and at d = 128 up to 73
+// d_down up to d, and at d = 128 up to 73, the interface's limit (three column
+// tiles would hold 96 in 120 KB of LDS)
 bool bwd_rope_mfma_supported(int d, int dd, bool bf16) {
     return bf16 && ((d == 64 && dd <= 64) || (d == 128 && dd <= 73));
 }
