@@ -61,13 +61,13 @@ CSRC = os.path.join(ROOT, "paper_2606_18587_amd", "csrc")
 MEASURED_TRAFFIC = {
     "prefill": {"files": ["dar_api.hip", "dar_common.hpp", "dar_kernels.hpp", "latent.hip",
                           "prefill_mfma.hip"],
-                "sha256_16": "3f4b701fa890b594", "bytes": 126122004},
+                "sha256_16": "ce50aaaf04819d79", "bytes": 126136702},
     "decode": {"files": ["dar_api.hip", "dar_common.hpp", "dar_kernels.hpp", "decode.hip",
                          "decode_mfma.hip"],
-               "sha256_16": "487397547ecf0358", "bytes": 563903519},
+               "sha256_16": "46b16e029ed7f64f", "bytes": 563867936},
     "backward": {"files": ["dar_api.hip", "dar_common.hpp", "dar_kernels.hpp", "mfma_common.hpp",
                            "backward.hip", "backward_mfma.hip"],
-                 "sha256_16": "15349d2b038086b3", "bytes": 502168977},
+                 "sha256_16": "096787b57555a7f4", "bytes": 500670007},
 }
 
 
